@@ -199,7 +199,7 @@ struct useries_server_s {
     int grid[BK_COUNT] = {0};
     int lds_limit = 0;
     // by the dynamic LDS sizes and the stencil half width
-    std::map<std::tuple<size_t, size_t, size_t, int, bool, int>, hipGraphExec_t> graphs;
+    std::map<std::tuple<size_t, size_t, size_t, int, int, int>, hipGraphExec_t> graphs;
     std::vector<hipGraph_t> graph_objs;
     std::chrono::steady_clock::time_point t0 = std::chrono::steady_clock::now();
 
@@ -248,9 +248,9 @@ struct useries_server_s {
 
     // the kernels of one step, in order, on the server stream
     // P: the stencil half width shared by the step's boxes, 0 if they differ;
-    // exact: some box evaluates leading far terms as Gaussians in its near part;
+    // exact: the most leading far terms a box evaluates as Gaussians in its near part;
     // bins: bit 0 some box bins in two launches, bit 1 some box in four
-    hipError_t enqueue_kernels(size_t lds, size_t lds_z, size_t lds_g, int P, bool exact,
+    hipError_t enqueue_kernels(size_t lds, size_t lds_z, size_t lds_g, int P, int exact,
                                int bins) {
         const bool bf = precision == USERIES_BF16X3;
         hipError_t e;
@@ -272,9 +272,9 @@ struct useries_server_s {
         return launch_displace_batch(d_table, d_desc, grid[BK_DISPLACE], st);
     }
 
-    hipError_t graph_for(size_t lds, size_t lds_z, size_t lds_g, int P, bool exact, int bins,
+    hipError_t graph_for(size_t lds, size_t lds_z, size_t lds_g, int P, int exact, int bins,
                          hipGraphExec_t* out) {
-        const std::tuple<size_t, size_t, size_t, int, bool, int> key(lds, lds_z, lds_g, P, exact,
+        const std::tuple<size_t, size_t, size_t, int, int, int> key(lds, lds_z, lds_g, P, exact,
                                                                      bins);
         auto it = graphs.find(key);
         if (it != graphs.end()) {
@@ -426,11 +426,11 @@ struct useries_server_s {
         for (int k = 0; k < BK_COUNT; ++k) T.off[k][0] = 0;
         size_t lds = 0, lds_z = 0, lds_g = 0;
         int P = -1;
-        bool exact = false;
+        int exact = 0;
         int bins = 0;
         for (int i = 0; i < nb; ++i) {
             Req* R = active[i];
-            exact = exact || R->hp.near_exact > 0;
+            exact = std::max(exact, R->hp.near_exact);
             bins |= R->local ? 1 : 2;
             T.slot[i] = R->slot;
             T.step[i] = R->step;

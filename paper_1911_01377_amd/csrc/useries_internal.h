@@ -249,8 +249,8 @@ hipError_t launch_bin_local_batch(const BatchTable* tab, const BoxDesc* desc, in
                                   hipStream_t st);
 hipError_t launch_colbuild_batch(const BatchTable* tab, const BoxDesc* desc, int grid,
                                  hipStream_t st);
-// exact: some box of the batch evaluates leading far terms as Gaussians (ne > 0)
-hipError_t launch_pair_batch(const BatchTable* tab, const BoxDesc* desc, int deg, bool exact,
+// ne: the most leading far terms that a box of the batch evaluates as Gaussians
+hipError_t launch_pair_batch(const BatchTable* tab, const BoxDesc* desc, int deg, int ne,
                              int grid, hipStream_t st);
 // P: the stencil half width of every box in the batch (compiled code for 3
 // and 5), or 0 when they differ

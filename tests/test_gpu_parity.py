@@ -371,6 +371,25 @@ def test_every_construction(construction, name, precision, tol):
             e_scale="parts", construction=construction, precision=precision)
 
 
+@pytest.mark.parametrize("construction,degree,ne", [
+    (USERIES_TABLE1_ROW3, 4, 8), (USERIES_TABLE1_ROW3, 5, 7), (USERIES_TABLE1_ROW3, 6, 6),
+    (USERIES_TABLE1_ROW3, 8, 4), (USERIES_TABLE1_ROW3, 9, 3), (USERIES_TABLE1_ROW1, 5, 2),
+    (USERIES_TABLE1_ROW1, 7, 1)])
+def test_counts_of_exact_gaussians(construction, degree, ne):
+    """Polynomial degrees that leave 1 to 8 exact Gaussians to the pair
+    kernel, which is compiled for 1, 2, 3, 5 and 8 of them (others rounded
+    up), in a cubic and a non-cubic cell, at the plain tolerances.  (Row 3
+    stays at degrees up to 9: its monomial coefficients of degree 11 and
+    above are too large for FP32 at 1e-5 in force.)"""
+    L = (300 / synth.WATER_DENSITY) ** (1 / 3)
+    xyz, q, box = synth.water_box(n_mol=300, L=L, seed=77)
+    for b in (box, (box[0], box[1] * 1.05, box[2])):
+        _, _, _, _, info = compare("water300/exact%d/degree%d" % (ne, degree), xyz, q, b, 9.0,
+                                   (28, 28, 28), 1e-6, 1e-5, construction=construction,
+                                   poly_degree=degree)
+        assert info["near_exact"] == ne
+
+
 def test_c1_at_other_bases():
     """The C1 construction solved on the host for b other than 2 (the
     smallest root of eq. 26 with w0 from eq. 25): b = 1.5 and 3."""

@@ -78,6 +78,28 @@ def test_single_evaluation_equals_plan(form, prec, e_tol, f_tol):
     assert np.array_equal(res["forces"], f)
 
 
+@pytest.mark.parametrize("degree", [5, 7])
+def test_exact_gaussians_equal_plan(degree):
+    """Table 1 row 2 (four or three exact Gaussians in the near part) through
+    the batched pair kernel, compiled for five and three: bitwise the plan's."""
+    need_gpu()
+    cons = N.USERIES_TABLE1_ROW2
+    cells = [small_water(216, 11), small_water(300, 12)]
+    srv = Server(256 << 20, max_slots=4, precision=USERIES_PLAIN_FP32, construction=cons,
+                 poly_degree=degree)
+    res = run_all(srv, cells, 1, 0.0, [5, 6])
+    srv.close()
+    dev = torch.device("cuda:0")
+    for (xyz, q, box, rc, grid), r in zip(cells, res):
+        plan = Plan(box, rc, grid, construction=cons, poly_degree=degree, spectral=0)
+        assert plan.info["near_exact"] == (4 if degree == 5 else 3)
+        e, f, _ = plan.eval(torch.from_numpy(xyz).to(dev), torch.from_numpy(q).to(dev))
+        torch.cuda.synchronize()
+        assert r["energies"][0] == float(e.cpu()[0])
+        assert np.array_equal(r["forces"], f.cpu().numpy())
+        plan.close()
+
+
 def test_step_with_both_binning_sequences():
     """A flat 256 x 256 x 19 A cell of 200,000 random charges (69 x 69
     columns: more than the two-launch binning takes, so it bins in four
