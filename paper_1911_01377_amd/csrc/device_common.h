@@ -47,6 +47,18 @@ __device__ __forceinline__ int small_div(int v, float inv_d) {
     return (int)(((float)v + 0.5f) * inv_d);
 }
 
+// v mod n for 0 <= v < 2n: v - n wraps to a large unsigned value when v < n
+__device__ __forceinline__ int mod_once(int v, int n) {
+    return (int)min((uint32_t)v, (uint32_t)(v - n));
+}
+
+// floor(v / d) for 0 <= v < 2^25 and 1 < d <= 128, m = magic_of(d): m d exceeds
+// 2^32 by less than d, so v m / 2^32 exceeds v / d by less than v d / (d 2^32)
+// < 1 / 128 <= 1 / d, and the floor is the same
+__device__ __forceinline__ int magic_div(int v, uint32_t m) {
+    return (int)__umulhi((uint32_t)v, m);
+}
+
 // number of set bits of m in the lanes below this one
 __device__ __forceinline__ int lanes_below(uint64_t m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),

@@ -33,28 +33,57 @@ constexpr int kBrick = 8;
 constexpr int kSpreadWaves = 8;                  // wavefronts per brick
 constexpr int kSpreadChunk = 64 * kSpreadWaves;  // candidates loaded per pass, one per thread
 
-__device__ __forceinline__ int floordiv(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
-__device__ __forceinline__ int ceildiv(int a, int b) { return a >= 0 ? (a + b - 1) / b : -((-a) / b); }
-__device__ __forceinline__ long long floordiv_ll(long long a, long long b) {
-    return a >= 0 ? a / b : -((-a + b - 1) / b);
-}
-__device__ __forceinline__ long long ceildiv_ll(long long a, long long b) {
-    return a >= 0 ? (a + b - 1) / b : -((-a) / b);
-}
-
-// columns along one axis that can hold charges touching grid points
+// columns along axis ax that can hold charges touching grid points
 // [X0, X0 + bn): charges whose stencil start lies in [X0 - P, X0 + bn + P - 1)
-__device__ __forceinline__ void cell_window(int X0, int bn, int P, int g, int nc, int* lo,
-                                            int* cnt) {
-    const int l = floordiv((X0 - P) * nc, g);
-    const int h = ceildiv((X0 + bn + P - 1) * nc, g) - 1;
+__device__ __forceinline__ void cell_window(const GridArgs& a, int ax, int X0, int bn, int P,
+                                            int* lo, int* cnt) {
+    const int g = a.g[ax], nc = a.nc[ax];
+    const int l = magic_div((X0 - P + g) * nc, a.mg[ax]) - nc;              // floor
+    const int h = magic_div((X0 + bn + P - 1) * nc + g - 1, a.mg[ax]) - 1;  // ceil - 1
     if (h - l + 1 >= nc) {
         *lo = 0;
         *cnt = nc;
     } else {
-        *lo = wrapi(l, nc);
+        *lo = wrap1(l, nc);
         *cnt = h - l + 1;
     }
+}
+
+// origin of brick bid (x fastest) of edge B, and its extent on the grid
+struct Brick {
+    int o[3], n[3];
+};
+__device__ __forceinline__ Brick brick_at(const GridArgs& a, int bid, int B,
+                                          const uint32_t mb[2]) {
+    const int nbx = (a.g[0] + B - 1) / B, nby = (a.g[1] + B - 1) / B;
+    const int r = nbx > 1 ? magic_div(bid, mb[0]) : bid;
+    const int z = nby > 1 ? magic_div(r, mb[1]) : r;
+    Brick k;
+    k.o[0] = (bid - r * nbx) * B;
+    k.o[1] = (r - z * nby) * B;
+    k.o[2] = z * B;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) k.n[ax] = min(B, a.g[ax] - k.o[ax]);
+    return k;
+}
+
+// acc[x] += X_c[x] yz[c] for the four charges c in order, X_c[x] in lane
+// 4 c + x of each 16-lane row of xw: the FMA reads it from there (a DPP row
+// broadcast as its first operand, which the compiler emits only as a separate
+// move).  The two wait states are those a DPP read needs after a vector write
+// of its source.
+__device__ __forceinline__ void spread_add4(float acc[4], float xw, const float yz[4]) {
+#define USERIES_FMAC(X, C, N)                                                                  \
+    "v_fmac_f32_dpp %" #X ", %4, %" #C " row_newbcast:" #N " row_mask:0xf bank_mask:0xf\n"
+    asm("s_nop 1\n" USERIES_FMAC(0, 5, 0) USERIES_FMAC(1, 5, 1) USERIES_FMAC(2, 5, 2)
+            USERIES_FMAC(3, 5, 3) USERIES_FMAC(0, 6, 4) USERIES_FMAC(1, 6, 5)
+                USERIES_FMAC(2, 6, 6) USERIES_FMAC(3, 6, 7) USERIES_FMAC(0, 7, 8)
+                    USERIES_FMAC(1, 7, 9) USERIES_FMAC(2, 7, 10) USERIES_FMAC(3, 7, 11)
+                        USERIES_FMAC(0, 8, 12) USERIES_FMAC(1, 8, 13) USERIES_FMAC(2, 8, 14)
+                            USERIES_FMAC(3, 8, 15)
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+        : "v"(xw), "v"(yz[0]), "v"(yz[1]), "v"(yz[2]), "v"(yz[3]));
+#undef USERIES_FMAC
 }
 
 }  // namespace
@@ -66,227 +95,254 @@ __device__ __forceinline__ void cell_window(int X0, int bn, int P, int g, int nc
 // chunks of one per thread, keeps those whose stencil touches the brick
 // (compacted in thread order within three classes: those meeting only the x
 // half 0 (x 0..3), both halves, only half 1 -- so the order is deterministic
-// and each half's charges are one contiguous run), stages their 3 x 8 weights
-// in LDS, and wavefront 4 h + u accumulates every fourth of half h's charges
-// from the u-th into its partial half brick (a dense 4 x 8 x 8 product per
-// charge; a charge whose stencil ends at brick position d meets both halves
-// only for 4 <= d <= 2P + 2, so at P = 3 about 60% of the charges are
-// accumulated by one half only); the four partials of each point are summed
-// in a fixed order at the end.
-// PT > 0: the stencil half width as a compile-time constant; PT = 0 takes it
-// from a.P.
-template <int PT>
+// and each half's charges are one contiguous run), evaluates their 3 x 8
+// weights into LDS (a wavefront takes one axis of 64 charges, a lane the 8
+// brick positions of one: no branches, two 16-byte stores), and wavefront
+// 4 h + u accumulates every fourth of half h's charges from the u-th into its
+// partial half brick (a dense 4 x 8 x 8 product per charge; a charge whose
+// stencil ends at brick position d meets both halves only for
+// 4 <= d <= 2P + 2, so at P = 3 about 60% of the charges are accumulated by
+// one half only); the four partials of each point are summed in a fixed order
+// at the end.
+//
+// Bound: VALU issue (77% of its slots on 90,180 charges, plain: 9,450
+// instructions per brick, 38% of them the accumulation, 28% the weights).  It
+// was 55.8 us there with 3 LDS reads per charge in the accumulation, branches
+// around every stencil point in the weights and 13 integer divisions per
+// wavefront, and is 41.1; 26,268 charges 19.1 -> 14.9, BF16X3 10.3 -> 8.4.
 __device__ __forceinline__ void spread_body(const GridArgs& a, int bid,
                                             const uint4* __restrict__ sorted,
                                             const int* __restrict__ zbin,
                                             const double* __restrict__ qstats,
                                             float* __restrict__ rho) {
-    __shared__ __align__(16) float sw[kSpreadChunk][3 * kBrick];   // rows of 96 B (16-byte stores)
+    // staged charges: their records, then their weights [x 8 | y 8 | z 8], each
+    // axis's inputs in its own 8 words; rows of 96 B (16-byte stores)
+    __shared__ __align__(16) float sw[kSpreadChunk][3 * kBrick];
     static_assert(kSpreadWaves == 8 && kBrick == 8, "four wavefronts per half brick; 8-wide rows");
     // the wavefronts' partial half bricks, summed after the last chunk (reuses
     // sw; rows of 65 so that the 8 partials a thread group reads lie in
     // different banks)
     float (*red)[4][65] = reinterpret_cast<float (*)[4][65]>(&sw[0][0]);
     static_assert(kSpreadWaves * 4 * 65 <= kSpreadChunk * 3 * kBrick, "red fits in sw");
-    __shared__ int pbeg[2 * kMaxWindowCols];       // first charge of each column piece
+    __shared__ int pbeg[2 * kMaxWindowCols];       // first charge of each non-empty column piece
     __shared__ int poff[2 * kMaxWindowCols + 1];   // prefix sums of the piece lengths
-    __shared__ int wtot[kSpreadWaves];
-    __shared__ int wcat[3][kSpreadWaves];
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    __shared__ int2 wtot[kSpreadWaves];
+    __shared__ int wcat[kSpreadWaves];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // wavefronts 4 h .. 4 h + 3 accumulate the x half h of the brick
     // (x 4 h .. 4 h + 3); lane (y, z) owns the four points of that row,
     // partial sums acc[x - 4 h]
     const int hx = w >> 2, ly = lane & 7, lz = lane >> 3;
     // the grid mean of the charge (removed at the end), loaded first
     const float mean = (float)(qstats[0] * a.inv_ngrid);
-    const int nbx = (a.g[0] + kBrick - 1) / kBrick, nby = (a.g[1] + kBrick - 1) / kBrick;
-    const int X0 = (bid % nbx) * kBrick, Y0 = ((bid / nbx) % nby) * kBrick,
-              Z0 = (bid / (nbx * nby)) * kBrick;
-    const int B0 = min(kBrick, a.g[0] - X0), B1 = min(kBrick, a.g[1] - Y0),
-              B2 = min(kBrick, a.g[2] - Z0);
-    const int P = PT > 0 ? PT : a.P, gz = a.g[2];
-    constexpr int KMAX = PT > 0 ? 2 * PT : 2 * kMaxStencilHalf;   // stencil points per axis
+    const Brick K = brick_at(a, bid, kBrick, a.mb8);
+    const int P = a.P, gz = a.g[2];
     int lo[2], cnt[2];
-    cell_window(X0, B0, P, a.g[0], a.nc[0], &lo[0], &cnt[0]);
-    cell_window(Y0, B1, P, a.g[1], a.nc[1], &lo[1], &cnt[1]);
+    cell_window(a, 0, K.o[0], K.n[0], P, &lo[0], &cnt[0]);
+    cell_window(a, 1, K.o[1], K.n[1], P, &lo[1], &cnt[1]);
     const int ncw = cnt[0] * cnt[1];
-    const int np = 2 * ncw;
     // z planes of the window: [zs, zs + zl) modulo gz
-    const int zl = B2 + 2 * P - 1;
-    const int zs = wrapi(Z0 - P, gz);
-    for (int k = tid; k < ncw; k += 64 * kSpreadWaves) {
-        const int col = wrapi(lo[1] + k / cnt[0], a.nc[1]) * a.nc[0] + wrapi(lo[0] + k % cnt[0], a.nc[0]);
+    const int zl = K.n[2] + 2 * P - 1;
+    const int zs = wrap1(K.o[2] - P, gz);
+    // candidate charge ranges of window column k = tid: at most two (the
+    // second only where the z window wraps)
+    static_assert(kMaxWindowCols <= 64 * kSpreadWaves, "one window column per thread");
+    int rb0 = 0, n0 = 0, rb1 = 0, n1 = 0;
+    if (tid < ncw) {
+        const int ky = small_div(tid, __builtin_amdgcn_rcpf((float)cnt[0]));
+        const int col = wrap1(lo[1] + ky, a.nc[1]) * a.nc[0] +
+                        wrap1(lo[0] + tid - ky * cnt[0], a.nc[0]);
         const int* zr = zbin + (size_t)col * (gz + 1);
-        int b0, e0, b1 = 0, e1 = 0;
         if (zl >= gz) {
-            b0 = zr[0];
-            e0 = zr[gz];
+            rb0 = zr[0];
+            n0 = zr[gz] - rb0;
         } else if (zs + zl <= gz) {
-            b0 = zr[zs];
-            e0 = zr[zs + zl];
+            rb0 = zr[zs];
+            n0 = zr[zs + zl] - rb0;
         } else {
-            b0 = zr[zs];
-            e0 = zr[gz];
-            b1 = zr[0];
-            e1 = zr[zs + zl - gz];
+            rb0 = zr[zs];
+            n0 = zr[gz] - rb0;
+            rb1 = zr[0];
+            n1 = zr[zs + zl - gz] - rb1;
         }
-        pbeg[2 * k] = b0;
-        pbeg[2 * k + 1] = b1;
-        poff[2 * k + 1] = e0 - b0;
-        poff[2 * k + 2] = e1 - b1;
     }
-    __syncthreads();
-    // inclusive prefix of the np <= 512 piece lengths: two per thread
+    // non-empty pieces stored compactly: exclusive scans over the threads of
+    // (pieces, charges), then each thread writes its pieces
+    int np = 0, total = 0;
     {
-        const int r0 = 2 * tid, r1 = 2 * tid + 1;
-        const int v0 = r0 < np ? poff[r0 + 1] : 0, v1 = r1 < np ? poff[r1 + 1] : 0;
-        const int incl = wave_incl_scan(v0 + v1);
-        if (lane == 63) wtot[w] = incl;
+        const int m = (n0 > 0) + (n1 > 0), len = n0 + n1;
+        const int im = wave_incl_scan(m), il = wave_incl_scan(len);
+        if (lane == 63) wtot[w] = make_int2(im, il);
         __syncthreads();
-        int wbase = 0;
-        for (int v = 0; v < w; ++v) wbase += wtot[v];
-        const int excl = wbase + incl - v0 - v1;
-        if (r0 < np) poff[r0 + 1] = excl + v0;
-        if (r1 < np) poff[r1 + 1] = excl + v0 + v1;
-        if (tid == 0) poff[0] = 0;
+        int M = im - m, O = il - len;
+#pragma unroll
+        for (int v = 0; v < kSpreadWaves; ++v) {
+            const int2 t = wtot[v];
+            M += v < w ? t.x : 0;
+            O += v < w ? t.y : 0;
+            np += t.x;
+            total += t.y;
+        }
+        if (n0 > 0) {
+            pbeg[M] = rb0;
+            poff[M] = O;
+        }
+        if (n1 > 0) {
+            pbeg[M + (n0 > 0)] = rb1;
+            poff[M + (n0 > 0)] = O + n0;
+        }
+        if (tid == 0) poff[np] = total;
         __syncthreads();
     }
-    const int total = poff[np];
-    const int X0s[3] = {X0, Y0, Z0};
-    const int Bs[3] = {B0, B1, B2};
+    np = __builtin_amdgcn_readfirstlane(np);
+    total = __builtin_amdgcn_readfirstlane(total);
 
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 
-    // candidate t of the window (loads are issued one chunk ahead)
-    auto fetch = [&](int t) {
+    // candidate t = base + tid of the window (loads are issued one chunk
+    // ahead).  The pieces of the wavefront's first and last candidate by
+    // counting the offsets at or below them, then each lane's by bisection
+    // between the two (a few pieces)
+    auto fetch = [&](int base) {
+        const int t0 = base + 64 * w, t = t0 + lane;
         uint4 c = make_uint4(0, 0, 0, 0);
-        if (t < total) {
-            int l = 0, h = np;                 // piece r with poff[r] <= t < poff[r + 1]
-            while (h - l > 1) {
-                const int mid = (l + h) >> 1;
-                if (poff[mid] <= t) l = mid; else h = mid;
+        if (t0 < total) {
+            int l = -1, h = 0;
+            for (int r0 = 0; r0 < np; r0 += 64) {
+                const int o = r0 + lane < np ? poff[r0 + lane] : 0x7fffffff;
+                const int cl = __popcll(__builtin_amdgcn_ballot_w64(o <= t0));
+                const int ch = __popcll(__builtin_amdgcn_ballot_w64(o <= t0 + 63));
+                l += cl;
+                h += ch;
             }
-            c = sorted[pbeg[l] + (t - poff[l])];
+            if (t < total) {
+                while (h - l > 1) {              // poff[l] <= t < poff[h]
+                    const int mid = (l + h) >> 1;
+                    if (poff[mid] <= t) l = mid; else h = mid;
+                }
+                c = sorted[pbeg[l] + (t - poff[l])];
+            }
         }
         return c;
     };
-    uint4 next = fetch(tid);
-    for (int base = 0; base < total; base += kSpreadChunk) {
-        const int t = base + tid;
-        bool touch = false;
-        int cat = 0;
-        int gi[3];
-        float f[3];
-        float qj = 0.0f;
-        const uint4 c = next;
-        if (base + kSpreadChunk < total) next = fetch(t + kSpreadChunk);
-        if (t < total) {
-            grid_coord(c.x, a.g[0], &gi[0], &f[0]);
-            grid_coord(c.y, a.g[1], &gi[1], &f[1]);
-            grid_coord(c.z, a.g[2], &gi[2], &f[2]);
-            qj = __uint_as_float(c.w);
-            touch = true;
-            int d[3];   // last stencil point's brick position (first: d - 2P + 1)
+    // brick position of a charge's last stencil point: cell + sh modulo the axis
+    int sh[3];
 #pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-                d[ax] = wrap1(gi[ax] - (X0s[ax] - P), a.g[ax]);
-                touch = touch && d[ax] <= Bs[ax] + 2 * P - 2;
-            }
-            // x halves met: 0 (x 0..3) only, both, 1 (x 4 .. B0 - 1) only
-            const bool h0 = d[0] - 2 * P + 1 <= 3, h1 = d[0] >= 4 && B0 > 4;
-            cat = h0 ? (h1 ? 1 : 0) : 2;
-        }
+    for (int ax = 0; ax < 3; ++ax) sh[ax] = wrap1(P - K.o[ax], a.g[ax]);
+    uint4 next = fetch(0);
+    for (int base = 0; base < total; base += kSpreadChunk) {
+        const uint4 c = next;
+        if (base + kSpreadChunk < total) next = fetch(base + kSpreadChunk);
+        const int d0 = mod_once(cell_coord(c.x, a.g[0]) + sh[0], a.g[0]);
+        const int d1 = mod_once(cell_coord(c.y, a.g[1]) + sh[1], a.g[1]);
+        const int d2 = mod_once(cell_coord(c.z, a.g[2]) + sh[2], a.g[2]);
+        const bool touch = base + tid < total && d0 <= K.n[0] + 2 * P - 2 &&
+                           d1 <= K.n[1] + 2 * P - 2 && d2 <= K.n[2] + 2 * P - 2;
+        // x halves met: 0 (x 0..3) only, both, 1 (x 4 ..) only
+        const bool h0 = d0 - 2 * P + 1 <= 3, h1 = d0 >= 4 && K.n[0] > 4;
         // compaction in thread order within each x-half class, the classes
         // one after the other: half 0's charges are rows [0, n0 + n01), half
-        // 1's rows [n0, nst)
-        const uint64_t mc[3] = {__ballot(touch && cat == 0), __ballot(touch && cat == 1),
-                                __ballot(touch && cat == 2)};
-        if (lane < 3) wcat[lane][w] = __popcll(lane == 0 ? mc[0] : lane == 1 ? mc[1] : mc[2]);
+        // 1's rows [n0, nst).  The wavefronts' three counts travel in one
+        // word, 10 bits each
+        const uint64_t mt = __builtin_amdgcn_ballot_w64(touch);
+        const uint64_t m0 = __builtin_amdgcn_ballot_w64(h0), m1 = __builtin_amdgcn_ballot_w64(h1);
+        const uint64_t mA = mt & m0 & ~m1, mB = mt & m0 & m1, mC = mt & ~m0;
+        static_assert(kSpreadChunk < 1024, "10 bits per count");
+        if (lane == 0) wcat[w] = __popcll(mA) | __popcll(mB) << 10 | __popcll(mC) << 20;
         __syncthreads();
-        int ncat[3] = {0, 0, 0}, bcat[3] = {0, 0, 0};
+        int below = 0, all = 0;
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int v = 0; v < kSpreadWaves; ++v) {
-                bcat[k] += v < w ? wcat[k][v] : 0;
-                ncat[k] += wcat[k][v];
-            }
-        const int nst = ncat[0] + ncat[1] + ncat[2];
-        // the touching charges' records: record s in the first 16 bytes of
-        // weight row s
+        for (int v = 0; v < kSpreadWaves; ++v) {
+            const int k = wcat[v];
+            below += v < w ? k : 0;
+            all += k;
+        }
+        below = __builtin_amdgcn_readfirstlane(below);
+        all = __builtin_amdgcn_readfirstlane(all);
+        const int nA = all & 1023, nAB = nA + ((all >> 10) & 1023), nst = nAB + (all >> 20);
+        // the touching charges' coordinates: x in word 0 of the charge's row,
+        // y and the charge in words 8 and 9, z in word 16
         if (touch) {
-            const int cb = cat == 0 ? 0 : cat == 1 ? ncat[0] : ncat[0] + ncat[1];
-            const uint64_t mm = cat == 0 ? mc[0] : cat == 1 ? mc[1] : mc[2];
-            *reinterpret_cast<uint4*>(sw[cb + bcat[cat] + lanes_below(mm)]) = c;
+            const uint64_t mm = !h0 ? mC : h1 ? mB : mA;
+            const int first = !h0 ? nAB + (below >> 20)
+                                  : h1 ? nA + ((below >> 10) & 1023) : (below & 1023);
+            uint32_t* row = reinterpret_cast<uint32_t*>(sw[first + lanes_below(mm)]);
+            row[0] = c.x;
+            *reinterpret_cast<uint2*>(row + kBrick) = make_uint2(c.y, c.w);
+            row[2 * kBrick] = c.z;
         }
         __syncthreads();
-        if (tid < nst) {
-            // thread s: the 3 x 8 brick weights of staged charge s (row s is
-            // its own until the next barrier): zero, then the 2P stencil points
-            // of each axis at their brick positions (k - k0) mod g
-            float* row = sw[tid];
-            const uint4 cs = *reinterpret_cast<const uint4*>(row);
-            grid_coord(cs.x, a.g[0], &gi[0], &f[0]);
-            grid_coord(cs.y, a.g[1], &gi[1], &f[1]);
-            grid_coord(cs.z, a.g[2], &gi[2], &f[2]);
-            qj = __uint_as_float(cs.w);
+        // unit u: axis u % 3 of staged charges 64 (u / 3) + lane.  Brick
+        // position b is stencil point k = b + k0 modulo the axis, within
+        // the stencil for k < 2P; one subtraction covers the modulus on axes
+        // of at least brick + 2P - 1 points, where at most one of b + k0 and
+        // b + k0 - g can be a stencil point for the whole brick
+        const int nu = 3 * ((nst + 63) >> 6);
+        for (int u = w; u < nu; u += kSpreadWaves) {
+            const int grp = magic_div(u, 0x55555556u), ax = u - 3 * grp;
+            const int s = 64 * grp + lane;
+            if (s < nst) {
+                float* row = sw[s] + kBrick * ax;
+                const int g = ax == 0 ? a.g[0] : ax == 1 ? a.g[1] : a.g[2];
+                const int o = ax == 0 ? K.o[0] : ax == 1 ? K.o[1] : K.o[2];
+                const float hs = ax == 0 ? a.hs[0] : ax == 1 ? a.hs[1] : a.hs[2];
+                const float cw = ax == 0 ? a.cw[0] : ax == 1 ? a.cw[1] : a.cw[2];
+                int gi;
+                float f;
+                grid_coord(__float_as_uint(row[0]), g, &gi, &f);
+                const float cf = (float)(P - 1) + f;
+                const float sc = ax == 1 ? cw * row[1] : cw;
+                const float e2 = -hs * 1.44269504f;   // exp(-t^2 hs) = 2^(t^2 e2)
+                const uint32_t k0 = wrap1(o - gi + P - 1, g);
+                float wt[kBrick];
+                auto eval = [&](auto&& kof) {
 #pragma unroll
-            for (int b = 0; b < 3 * kBrick; b += 4)
-                *reinterpret_cast<float4*>(row + b) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-                const int k0 = wrap1(X0s[ax] - gi[ax] + P - 1, a.g[ax]);
-                const float c = (float)(P - 1) + f[ax];
-                const float sc = ax == 1 ? a.cw[ax] * qj : a.cw[ax];
-                const float e2 = -a.hs[ax] * 1.44269504f;   // exp(-t^2 hs) = 2^(t^2 e2)
-#pragma unroll
-                for (int k = 0; k < KMAX; ++k) {
-                    if (PT > 0 || k < 2 * P) {
-                        int b = k - k0;
-                        if (b < 0) b += a.g[ax];
-                        if (b < Bs[ax]) {
-                            const float t = (float)k - c;
-                            row[ax * kBrick + b] = sc * __builtin_amdgcn_exp2f(t * t * e2);
-                        }
+                    for (int b = 0; b < kBrick; ++b) {
+                        const uint32_t k = kof(b);
+                        const float t = (float)(int)k - cf;
+                        const float v = sc * __builtin_amdgcn_exp2f(t * t * e2);
+                        wt[b] = k < (uint32_t)(2 * P) ? v : 0.0f;
                     }
+                };
+                if (g >= kBrick + 2 * P - 1) {
+                    const uint32_t k1 = k0 < (uint32_t)(2 * P) ? k0 : k0 - g;
+                    eval([&](int b) { return k1 + b; });
+                } else {
+                    eval([&](int b) { return min(k0 + b, k0 + b - g); });
                 }
+                *reinterpret_cast<float4*>(row) = make_float4(wt[0], wt[1], wt[2], wt[3]);
+                *reinterpret_cast<float4*>(row + 4) = make_float4(wt[4], wt[5], wt[6], wt[7]);
             }
         }
         __syncthreads();
         // the staged charges of this wavefront's x half, every fourth one, in
-        // staged order, two at a time with their LDS reads issued together;
-        // per charge the half's four x weights (one 16-byte read, the same
-        // address on every lane), the lane's y and z weights, one y z product
-        // and four FMAs
-        auto wts = [&](int sidx, float4& X, float& Y, float& Z) {
+        // staged order, four per pass: one 4-byte read gives the four charges'
+        // x weights of the half (lane 4 c + x of each 16-lane row: weight x of
+        // charge c), which the FMAs take from their lane by a DPP row
+        // broadcast; per charge then the lane's y and z weights, one y z
+        // product and four FMAs
+        const int hend = hx == 0 ? nAB : nst;
+        int sidx = (hx == 0 ? 0 : nA) + (w & 3);
+        const int xc = (lane >> 2) & 3, xo = 4 * hx + (lane & 3);
+        for (; sidx + 12 < hend; sidx += 16) {
             const float* row = sw[sidx];
-            X = *reinterpret_cast<const float4*>(row + 4 * hx);
-            Y = row[kBrick + ly];
-            Z = row[2 * kBrick + lz];
-        };
-        auto add = [&](const float4 X, const float Y, const float Z) {
-            const float yz = Y * Z;
+            const float xw = row[4 * xc * (3 * kBrick) + xo];
+            float yz[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                yz[c] = row[4 * c * (3 * kBrick) + kBrick + ly] *
+                        row[4 * c * (3 * kBrick) + 2 * kBrick + lz];
+            spread_add4(acc, xw, yz);
+        }
+        for (; sidx < hend; sidx += 4) {
+            const float* row = sw[sidx];
+            const float4 X = *reinterpret_cast<const float4*>(row + 4 * hx);
+            const float yz = row[kBrick + ly] * row[2 * kBrick + lz];
             acc[0] = fmaf(X.x, yz, acc[0]);
             acc[1] = fmaf(X.y, yz, acc[1]);
             acc[2] = fmaf(X.z, yz, acc[2]);
             acc[3] = fmaf(X.w, yz, acc[3]);
-        };
-        // (uniform per wavefront: loop control in scalar registers)
-        const int hend = __builtin_amdgcn_readfirstlane(hx == 0 ? ncat[0] + ncat[1] : nst);
-        int sidx = __builtin_amdgcn_readfirstlane((hx == 0 ? 0 : ncat[0]) + (w & 3));
-        for (; sidx + 4 < hend; sidx += 8) {
-            float4 X0w, X1w;
-            float Y0w, Z0w, Y1w, Z1w;
-            wts(sidx, X0w, Y0w, Z0w);
-            wts(sidx + 4, X1w, Y1w, Z1w);
-            add(X0w, Y0w, Z0w);
-            add(X1w, Y1w, Z1w);
-        }
-        if (sidx < hend) {
-            float4 Xw;
-            float Yw, Zw;
-            wts(sidx, Xw, Yw, Zw);
-            add(Xw, Yw, Zw);
         }
         __syncthreads();
     }
@@ -303,27 +359,24 @@ __device__ __forceinline__ void spread_body(const GridArgs& a, int bid,
     float v = red[4 * h][k][l];
 #pragma unroll
     for (int u = 1; u < 4; ++u) v += red[4 * h + u][k][l];
-    if (px < B0 && py < B1 && pz < B2)
-        rho[((size_t)(Z0 + pz) * a.g[1] + (Y0 + py)) * a.g[0] + X0 + px] = v - mean;
+    if (px < K.n[0] && py < K.n[1] && pz < K.n[2])
+        rho[((size_t)(K.o[2] + pz) * a.g[1] + (K.o[1] + py)) * a.g[0] + K.o[0] + px] = v - mean;
 }
 
-template <int PT>
 __global__ void __launch_bounds__(64 * kSpreadWaves) k_spread(int nb,
                                                               const int* __restrict__ zbin,
                                                               const double* __restrict__ qstats,
                                                               const uint4* __restrict__ sorted,
                                                               float* __restrict__ rho, GridArgs a) {
     const int item = xcd_item(blockIdx.x, nb);
-    if (item < nb) spread_body<PT>(a, item, sorted, zbin, qstats, rho);
+    if (item < nb) spread_body(a, item, sorted, zbin, qstats, rho);
 }
 
-// PT > 0 only when every box of the batch has stencil half width PT
-template <int PT>
 __global__ void __launch_bounds__(64 * kSpreadWaves) k_spread_batch(
         const BatchTable* __restrict__ tab, const BoxDesc* __restrict__ desc) {
     batch_for(tab, BK_SPREAD, [&](int i, int item) {
         const BoxDesc& d = desc[tab->slot[i]];
-        spread_body<PT>(d.grid, item, d.sorted, d.zbin, d.qstats, d.rho);
+        spread_body(d.grid, item, d.sorted, d.zbin, d.qstats, d.rho);
     });
 }
 
@@ -398,9 +451,8 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
     int* pbeg = reinterpret_cast<int*>(lds + LL.pbeg);
     int* poff = reinterpret_cast<int*>(lds + LL.poff);
     int* wtot = reinterpret_cast<int*>(lds + LL.wtot);
-    const int nbx = (a.g[0] + GB - 1) / GB, nby = (a.g[1] + GB - 1) / GB;
-    const int X0 = (bid % nbx) * GB, Y0 = ((bid / nbx) % nby) * GB, Z0 = (bid / (nbx * nby)) * GB;
-    const int B0 = min(GB, a.g[0] - X0), B1 = min(GB, a.g[1] - Y0), B2 = min(GB, a.g[2] - Z0);
+    const Brick K = brick_at(a, bid, GB, GB == 8 ? a.mb8 : a.mb4);
+    const int X0 = K.o[0], Y0 = K.o[1], Z0 = K.o[2], B0 = K.n[0], B1 = K.n[1], B2 = K.n[2];
     const int E0 = B0 + P2 - 1, E1 = B1 + P2 - 1, E2 = B2 + P2 - 1;
     // potential on the brick and halo: local (hx, hy, hz) = global (X0 - P + 1 + hx, ...)
     // approximate reciprocals: (idx + 1/2) / E stays 1 / (2E) from an integer
@@ -410,12 +462,15 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
     // thread): the charge range of the brick's z-planes in each, loaded first
     // so that these loads are in flight with the halo's
     static_assert(kGatherMaxPieces <= kGatherThreads, "one column per thread");
-    const int cxl = X0 * a.nc[0] / a.g[0], cxh = ((X0 + B0) * a.nc[0] + a.g[0] - 1) / a.g[0] - 1;
-    const int cyl = Y0 * a.nc[1] / a.g[1], cyh = ((Y0 + B1) * a.nc[1] + a.g[1] - 1) / a.g[1] - 1;
+    const int cxl = magic_div(X0 * a.nc[0], a.mg[0]),
+              cxh = magic_div((X0 + B0) * a.nc[0] + a.g[0] - 1, a.mg[0]) - 1;
+    const int cyl = magic_div(Y0 * a.nc[1], a.mg[1]),
+              cyh = magic_div((Y0 + B1) * a.nc[1] + a.g[1] - 1, a.mg[1]) - 1;
     const int cxn = cxh - cxl + 1, np = cxn * (cyh - cyl + 1);
     int zb = 0, ze = 0;
     if (tid < np) {
-        const int col = (cyl + tid / cxn) * a.nc[0] + cxl + tid % cxn;
+        const int ky = small_div(tid, __builtin_amdgcn_rcpf((float)cxn));
+        const int col = (cyl + ky) * a.nc[0] + cxl + tid - ky * cxn;
         const int* zr = zbin + (size_t)col * (a.g[2] + 1);
         zb = zr[Z0];
         ze = zr[Z0 + B2];
@@ -622,13 +677,8 @@ hipError_t launch_spread(const GridArgs& a, const uint4* sorted, const int* zbin
                          const double* qstats, float* rho, hipStream_t st) {
     const int nb = ((a.g[0] + kBrick - 1) / kBrick) * ((a.g[1] + kBrick - 1) / kBrick) *
                    ((a.g[2] + kBrick - 1) / kBrick);
-    const dim3 grid(xcd_blocks(nb)), block(64 * kSpreadWaves);
-    if (a.P == 3)
-        hipLaunchKernelGGL(k_spread<3>, grid, block, 0, st, nb, zbin, qstats, sorted, rho, a);
-    else if (a.P == 5)
-        hipLaunchKernelGGL(k_spread<5>, grid, block, 0, st, nb, zbin, qstats, sorted, rho, a);
-    else
-        hipLaunchKernelGGL(k_spread<0>, grid, block, 0, st, nb, zbin, qstats, sorted, rho, a);
+    hipLaunchKernelGGL(k_spread, dim3(xcd_blocks(nb)), dim3(64 * kSpreadWaves), 0, st, nb, zbin,
+                       qstats, sorted, rho, a);
     return hipGetLastError();
 }
 
@@ -658,15 +708,9 @@ hipError_t launch_gather(const GridArgs& a, const uint4* sorted, const int* perm
     return hipGetLastError();
 }
 
-hipError_t launch_spread_batch(const BatchTable* tab, const BoxDesc* desc, int P, int grid,
+hipError_t launch_spread_batch(const BatchTable* tab, const BoxDesc* desc, int grid,
                                hipStream_t st) {
-    const dim3 g(grid), b(64 * kSpreadWaves);
-    if (P == 3)
-        hipLaunchKernelGGL(k_spread_batch<3>, g, b, 0, st, tab, desc);
-    else if (P == 5)
-        hipLaunchKernelGGL(k_spread_batch<5>, g, b, 0, st, tab, desc);
-    else
-        hipLaunchKernelGGL(k_spread_batch<0>, g, b, 0, st, tab, desc);
+    hipLaunchKernelGGL(k_spread_batch, dim3(grid), dim3(64 * kSpreadWaves), 0, st, tab, desc);
     return hipGetLastError();
 }
 

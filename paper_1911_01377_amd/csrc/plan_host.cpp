@@ -324,6 +324,11 @@ int build_host_plan(HostPlan* hp, const double box[3], double r_c, double b, dou
         const double ss = ratio * h;
         p.sigma_s[a] = ss;
         ga.g[a] = ca.g[a] = grid[a];
+        ga.mg[a] = magic_of(grid[a]);
+        if (a < 2) {
+            ga.mb8[a] = magic_of((grid[a] + 7) / 8);
+            ga.mb4[a] = magic_of((grid[a] + 3) / 4);
+        }
         // padded to the MFMA K step: 4 (FP32, tiles of 16) or 32 (BF16)
         ca.gp[a] = bf ? (grid[a] + 31) / 32 * 32 : (grid[a] + 15) / 16 * 16;
         ga.hs[a] = (float)(h * h / (2.0 * ss * ss));

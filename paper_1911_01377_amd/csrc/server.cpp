@@ -265,7 +265,7 @@ struct useries_server_s {
         if ((bins & 1) && (e = launch_colbuild_batch(d_table, d_desc, grid[BK_COLBUILD], st)))
             return e;
         if ((e = launch_pair_batch(d_table, d_desc, popts.poly_degree, exact, grid[BK_PAIR], st))) return e;
-        if ((e = launch_spread_batch(d_table, d_desc, P, grid[BK_SPREAD], st))) return e;
+        if ((e = launch_spread_batch(d_table, d_desc, grid[BK_SPREAD], st))) return e;
         if ((e = launch_conv_xy_batch(d_table, d_desc, bf, lds, grid[BK_CONV_XY], st))) return e;
         if ((e = launch_conv_z_batch(d_table, d_desc, bf, lds_z, grid[BK_CONV_Z], st))) return e;
         if ((e = launch_gather_batch(d_table, d_desc, P, lds_g, grid[BK_GATHER], st))) return e;

@@ -99,6 +99,12 @@ struct PairArgs {
     float eau[kMaxExact], egu[kMaxExact];
 };
 
+// ceil(2^32 / d): the multiplier of magic_div (device_common.h); 0 for d = 1,
+// which is not divided by
+constexpr uint32_t magic_of(uint32_t d) {
+    return d > 1 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u;
+}
+
 struct GridArgs {
     int n;
     int g[3];             // grid points per axis
@@ -108,6 +114,10 @@ struct GridArgs {
     float cw[3];          // h / (sqrt(2 pi) sigma_s): weight prefactor per axis
     float dws[3];         // 2 hs / h: derivative factor of the weights per axis
     double inv_ngrid;     // 1 / (gx gy gz)
+    // magic_of of the divisors a block's brick and columns need (an integer
+    // division costs a wavefront about 40 instructions)
+    uint32_t mg[3];       // g
+    uint32_t mb8[2], mb4[2];   // bricks of edge 8 and 4 along x and y
 };
 
 constexpr int kMaxSpecRank = 17;   // Fourier modes per axis of the spectral wide terms
@@ -252,16 +262,15 @@ hipError_t launch_colbuild_batch(const BatchTable* tab, const BoxDesc* desc, int
 // ne: the most leading far terms that a box of the batch evaluates as Gaussians
 hipError_t launch_pair_batch(const BatchTable* tab, const BoxDesc* desc, int deg, int ne,
                              int grid, hipStream_t st);
-// P: the stencil half width of every box in the batch (compiled code for 3
-// and 5), or 0 when they differ
-hipError_t launch_spread_batch(const BatchTable* tab, const BoxDesc* desc, int P, int grid,
+hipError_t launch_spread_batch(const BatchTable* tab, const BoxDesc* desc, int grid,
                                hipStream_t st);
 hipError_t launch_conv_xy_batch(const BatchTable* tab, const BoxDesc* desc, int bf16x3,
                                 size_t lds, int grid, hipStream_t st);
 hipError_t launch_conv_z_batch(const BatchTable* tab, const BoxDesc* desc, int bf16x3, size_t lds,
                                int grid, hipStream_t st);
-// lds >= gather_lds_bytes(P) of every box in the batch; a box's items are
-// its bricks and then one that writes its energy total to energies[step]
+// P: the stencil half width of every box in the batch (compiled code for 3
+// and 5), or 0 when they differ; lds >= gather_lds_bytes(P) of every box in
+// it; a box's items are its bricks and then one that writes its energy total to energies[step]
 hipError_t launch_gather_batch(const BatchTable* tab, const BoxDesc* desc, int P, size_t lds,
                                int grid, hipStream_t st);
 // dynamic LDS of one gather block for stencil half width P

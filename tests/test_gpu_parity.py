@@ -77,6 +77,20 @@ def test_stencil_widths(P, ratio):
             stencil_half=P, sigma_s_over_h=ratio)
 
 
+@pytest.mark.parametrize("form,n_mol,grid", [
+    ("plain", 137, (16, 17, 18)), ("plain", 137, (18, 16, 17)), ("plain", 137, (17, 23, 24)),
+    ("bf16x3", 73, (12, 13, 14)), ("bf16x3", 73, (14, 12, 13)), ("bf16x3", 73, (15, 16, 17))])
+def test_stencil_and_brick_about_as_wide_as_the_grid(form, n_mol, grid):
+    """Axes of about brick + stencil points (8 + 2P - 1: 17 plain, 13 BF16X3),
+    where a charge's stencil can meet a spreading brick from both sides of the
+    periodic boundary, and bricks cut to 1 to 7 points."""
+    L = (n_mol / synth.WATER_DENSITY) ** (1 / 3)
+    xyz, q, box = synth.water_box(n_mol=n_mol, L=L, seed=17)
+    tol = (1e-6, 1e-5) if form == "plain" else (1e-3, 1e-3)
+    compare("water%d/%s/%s" % (n_mol, form, grid), xyz, q, box, 0.45 * L, grid, tol[0], tol[1],
+            precision=USERIES_BF16X3 if form == "bf16x3" else 0)
+
+
 def test_orthorhombic_box_and_grid():
     rng = np.random.default_rng(4)
     box = (20.0, 23.5, 27.0)
