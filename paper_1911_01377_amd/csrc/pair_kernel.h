@@ -303,7 +303,8 @@ __device__ __forceinline__ void pair_body(const PairArgs& a, int I, const uint4*
         }
     }
     // bounding box of the i-cluster (fixed point, offsets from its first
-    // charge), as a centre and half extents.  Per axis the periodic distance
+    // charge; unsigned, as a sparse cluster may extend over more than half the
+    // cell), as a centre and half extents.  Per axis the periodic distance
     // of a candidate from any i-charge is at least its periodic distance from
     // the centre minus the half extent, so a candidate whose such distances
     // put it r_c or more from the box meets no i-charge within r_c and is
@@ -334,9 +335,9 @@ __device__ __forceinline__ void pair_body(const PairArgs& a, int I, const uint4*
             ibox[0] = (int)(c0.x + (uint32_t)((bl[0] + bh[0]) / 2));
             ibox[1] = (int)(c0.y + (uint32_t)((bl[1] + bh[1]) / 2));
             ibox[2] = (int)(c0.z + (uint32_t)((bl[2] + bh[2]) / 2));
-            ibox[3] = (bh[0] - bl[0]) / 2 + 1;
-            ibox[4] = (bh[1] - bl[1]) / 2 + 1;
-            ibox[5] = (bh[2] - bl[2]) / 2 + 1;
+            ibox[3] = (int)(((uint32_t)bh[0] - (uint32_t)bl[0]) >> 1) + 1;
+            ibox[4] = (int)(((uint32_t)bh[1] - (uint32_t)bl[1]) >> 1) + 1;
+            ibox[5] = (int)(((uint32_t)bh[2] - (uint32_t)bl[2]) >> 1) + 1;
         }
     }
     int nr = 0, tot = 0;
@@ -426,7 +427,8 @@ __device__ __forceinline__ void pair_body(const PairArgs& a, int I, const uint4*
     // the test runs in those units (the reach r_c + margin scaled to them, no
     // per-candidate scaling), otherwise in A per axis
     const uint32_t cenx = (uint32_t)ibox[0], ceny = (uint32_t)ibox[1], cenz = (uint32_t)ibox[2];
-    const float hxu = (float)ibox[3], hyu = (float)ibox[4], hzu = (float)ibox[5];
+    const float hxu = (float)(uint32_t)ibox[3], hyu = (float)(uint32_t)ibox[4],
+                hzu = (float)(uint32_t)ibox[5];
     const float hx = CM == 1 ? hxu : hxu * sx, hy = CM == 1 ? hyu : hyu * sy,
                 hz = CM == 1 ? hzu : hzu * sz;
     const float rcm2 = CM == 1 ? a.rcm2 * isx * isx : a.rcm2;

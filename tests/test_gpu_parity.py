@@ -91,6 +91,17 @@ def test_stencil_and_brick_about_as_wide_as_the_grid(form, n_mol, grid):
             precision=USERIES_BF16X3 if form == "bf16x3" else 0)
 
 
+@pytest.mark.parametrize("n_mol,seed", [(73, 17), (20, 3), (3, 1)])
+def test_clusters_longer_than_half_the_cell(n_mol, seed):
+    """A few waters in cells of 8.4 to 13 A: a sparse column's clusters can
+    extend over more than half the cell along z (the pair kernel's bounding
+    box of the i-cluster)."""
+    L = max(8.4, (n_mol / synth.WATER_DENSITY) ** (1 / 3))
+    xyz, q, box = synth.water_box(n_mol=n_mol, L=L, seed=seed)
+    compare("water%d/sparse" % n_mol, xyz, q, box, 0.45 * L, (16, 16, 16), 1e-6, 1e-5,
+            e_scale="parts")
+
+
 def test_orthorhombic_box_and_grid():
     rng = np.random.default_rng(4)
     box = (20.0, 23.5, 27.0)
