@@ -239,8 +239,10 @@ __device__ __forceinline__ void spread_body(const GridArgs& a, int bid,
         const int d2 = mod_once(cell_coord(c.z, a.g[2]) + sh[2], a.g[2]);
         const bool touch = base + tid < total && d0 <= K.n[0] + 2 * P - 2 &&
                            d1 <= K.n[1] + 2 * P - 2 && d2 <= K.n[2] + 2 * P - 2;
-        // x halves met: 0 (x 0..3) only, both, 1 (x 4 ..) only
-        const bool h0 = d0 - 2 * P + 1 <= 3, h1 = d0 >= 4 && K.n[0] > 4;
+        // x halves met: 0 (x 0..3) only, both, 1 (x 4 ..) only; half 1 also
+        // from its far side, where the stencil wraps around a narrow axis
+        const bool h0 = d0 - 2 * P + 1 <= 3,
+                   h1 = (d0 >= 4 || d0 - 2 * P + 1 + a.g[0] < kBrick) && K.n[0] > 4;
         // compaction in thread order within each x-half class, the classes
         // one after the other: half 0's charges are rows [0, n0 + n01), half
         // 1's rows [n0, nst).  The wavefronts' three counts travel in one

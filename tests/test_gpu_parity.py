@@ -79,6 +79,7 @@ def test_stencil_widths(P, ratio):
 
 @pytest.mark.parametrize("form,n_mol,grid", [
     ("plain", 137, (16, 17, 18)), ("plain", 137, (18, 16, 17)), ("plain", 137, (17, 23, 24)),
+    ("plain", 137, (15, 23, 24)), ("plain", 73, (10, 11, 12)), ("plain", 73, (13, 10, 14)),
     ("bf16x3", 73, (12, 13, 14)), ("bf16x3", 73, (14, 12, 13)), ("bf16x3", 73, (15, 16, 17))])
 def test_stencil_and_brick_about_as_wide_as_the_grid(form, n_mol, grid):
     """Axes of about brick + stencil points (8 + 2P - 1: 17 plain, 13 BF16X3),
