@@ -470,6 +470,8 @@ __global__ void __launch_bounds__(256) k_colsort_batch(const BatchTable* __restr
 // ------------------------------------------------------------ two-launch binning
 constexpr int kLocalBlocks = 4096;   // bin_local blocks whose prefixes colbuild reads
 constexpr int kLocalRun = kLocalBlocks / 256;
+constexpr int kZBuckets = 512;       // z buckets of a column's sort, at most
+static_assert(kZBuckets >= kMaxGrid, "a bucket per grid plane at least");
 
 bool bin_local_ok(int n, int ncol) {
     const long long nb = ((long long)n + 255) / 256;
@@ -558,10 +560,19 @@ __device__ __forceinline__ void bin_local_body(const BinArgs& a, int b, const fl
 // Block c (column c): from P[b][c] and P[b][c + 1] of the nb bin_local blocks,
 // the column's first sorted position lo = sum_b P[b][c], its count and the
 // offset of each block's segment in the column's list; then its charges
-// gathered (list position k lies in the segment b with segoff[b] <= k <
-// segoff[b + 1]), sorted by (z, input index) -- up to 256 by counting ranks,
-// up to kSortCap by a bitonic sort in LDS, beyond by ranking from global
-// memory -- and written with the column's z-plane index and clusters.
+// gathered, sorted by (z, input index) and written with the column's z-plane
+// index and clusters.  Up to kSortCap charges are sorted by z buckets in LDS
+// (a whole number of buckets per grid plane, about 512 in all): a charge's
+// rank is its bucket's offset plus the keys of its bucket below its own, and
+// the offsets at the planes are the z-plane index; longer columns are ranked
+// from global memory.
+//
+// Bound: latency of two dependent rounds of scattered loads.  The block's LDS
+// (15 KB) lets all columns of the largest cells be resident at once.  With 68
+// KB of LDS (segment tables, sort arrays), two blocks per CU, ranks counted
+// against the whole column (bitonic beyond 256) and a search per charge for
+// its segment it took 22.4 us on 90,180 charges and 38.8 on 210,000, now 7.0
+// and 11.5 (26,268 charges 6.7 -> 5.3).
 // reduce_q: this block also reduces the charge sums (qstats_reduce).
 __device__ __forceinline__ void qstats_reduce(int nb, const double* __restrict__ qpart,
                                               double* __restrict__ qstats) {
@@ -589,19 +600,17 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
                                               uint2* __restrict__ cl_z, int* __restrict__ zbin,
                                               const double* __restrict__ qpart,
                                               double* __restrict__ qstats) {
-    __shared__ int segoff[kLocalBlocks + 1];
-    __shared__ int segbase[kLocalBlocks];      // slot of list position k: segbase[b] + k
-    __shared__ unsigned long long key[kSortCap];
-    __shared__ int pay[kSortCap];              // list position carried through the sort
-    __shared__ uint4 lrec[kSortCap];
-    __shared__ int lidx[kSortCap];
-    __shared__ uint32_t skz[kSortCap];         // z of the sorted charges
+    // record index of each list position, later the sorted charges' z
+    __shared__ uint32_t lslot[kSortCap];
+    __shared__ unsigned long long bkey[kSortCap];   // keys grouped by bucket
+    __shared__ int boff[kZBuckets + 1];             // bucket counts, then offsets
     __shared__ int wsum[2][4];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int stride = ncol + 1;
 
     // segment counts h_b = P[b][c + 1] - P[b][c] over a contiguous run of b
     // per thread; their exclusive scan (segment offsets) and the sum of P[b][c]
+    for (int k = t; k <= kZBuckets; k += 256) boff[k] = 0;
     const int run = (nb + 255) / 256;
     const int blo = min(t * run, nb), bhi = min(blo + run, nb);
     int h[kLocalRun], pc[kLocalRun];
@@ -627,15 +636,17 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
     for (int u = 0; u < wv; ++u) off += wsum[0][u];
     const int cnt = ((wsum[0][0] + wsum[0][1]) + wsum[0][2]) + wsum[0][3];
     const int lo = ((wsum[1][0] + wsum[1][1]) + wsum[1][2]) + wsum[1][3];
+    // list position off + j of segment b holds record 256 b + P[b][c] + j
+    if (cnt <= kSortCap) {
 #pragma unroll
-    for (int u = 0; u < kLocalRun; ++u) {
-        if (blo + u < bhi) {
-            segoff[blo + u] = off;
-            segbase[blo + u] = (blo + u) * 256 + pc[u] - off;
-            off += h[u];
+        for (int u = 0; u < kLocalRun; ++u) {
+            if (blo + u < bhi) {
+                const int r0 = (blo + u) * 256 + pc[u];
+                for (int j = 0; j < h[u]; ++j) lslot[off + j] = r0 + j;
+                off += h[u];
+            }
         }
     }
-    if (t == 0) segoff[nb] = cnt;
     if (reduce_q && wv == 1) qstats_reduce(nb, qpart, qstats);
 
     // cluster numbers: this column's from floor(lo / 8) + col, the next
@@ -650,119 +661,80 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
         return;
     }
     __syncthreads();
-    // the slot of list position k
-    auto slot_of = [&](int k) {
-        int l = 0, hh = nb;                  // last b with segoff[b] <= k
-        while (hh - l > 1) {
-            const int mid = (l + hh) >> 1;
-            if (segoff[mid] <= k) l = mid; else hh = mid;
-        }
-        return segbase[l] + k;
-    };
-    if (cnt <= 256) {
-        // one charge per thread, its rank counted against every key
-        unsigned long long mine = ~0ull;
-        uint4 c = make_uint4(0, 0, 0, 0);
-        int i = 0;
-        if (t < cnt) {
-            const int sl = slot_of(t);
-            c = coord[sl];
-            i = slots[sl];
-            mine = ((unsigned long long)c.z << 32) | (unsigned)i;
-            key[t] = mine;
-        }
-        __syncthreads();
-        if (t < cnt) {
-            int r0 = 0, r1 = 0, r2 = 0, r3 = 0, m = 0;
-#pragma unroll 4
-            for (; m + 4 <= cnt; m += 4) {
-                r0 += key[m] < mine;
-                r1 += key[m + 1] < mine;
-                r2 += key[m + 2] < mine;
-                r3 += key[m + 3] < mine;
-            }
-            for (; m < cnt; ++m) r0 += key[m] < mine;
-            const int r = (r0 + r1) + (r2 + r3);
-            perm[lo + r] = i;
-            sorted[lo + r] = c;
-            skz[r] = c.z;
-        }
-    } else if (cnt <= kSortCap) {
-        int m = 1;
-        while (m < cnt) m <<= 1;
-        for (int k = t; k < m; k += 256) {
+    const bool in_lds = cnt <= kSortCap;
+    uint32_t* skz = lslot;
+    if (in_lds) {
+        const int m = kZBuckets / gz, nz = gz * m;   // buckets per plane, in all
+        constexpr int kPer = kSortCap / 256;
+        uint4 c[kPer];
+        int i[kPer], bk[kPer], r[kPer];
+#pragma unroll
+        for (int v2 = 0; v2 < kPer; ++v2) {
+            const int k = t + 256 * v2;
             if (k < cnt) {
-                const int sl = slot_of(k);
-                const uint4 c = coord[sl];
-                const int i = slots[sl];
-                lrec[k] = c;
-                lidx[k] = i;
-                key[k] = ((unsigned long long)c.z << 32) | (unsigned)i;
-            } else {
-                key[k] = ~0ull;
+                const int sl = lslot[k];
+                c[v2] = coord[sl];
+                i[v2] = slots[sl];
+                bk[v2] = cell_coord(c[v2].z, nz);
+                r[v2] = atomicAdd(&boff[bk[v2]], 1);
             }
-            pay[k] = k;
         }
         __syncthreads();
-        for (int size = 2; size <= m; size <<= 1) {
-            for (int stride2 = size >> 1; stride2 > 0; stride2 >>= 1) {
-                for (int k = t; k < m; k += 256) {
-                    const int o = k ^ stride2;
-                    if (o > k) {
-                        const bool up = (k & size) == 0;
-                        const unsigned long long x = key[k], y = key[o];
-                        if ((x > y) == up) {
-                            key[k] = y;
-                            key[o] = x;
-                            const int pk = pay[k];
-                            pay[k] = pay[o];
-                            pay[o] = pk;
-                        }
-                    }
-                }
-                __syncthreads();
+        // counts to offsets: two buckets per thread
+        static_assert(kZBuckets == 512, "two buckets per thread");
+        const int b0 = boff[2 * t], b1 = boff[2 * t + 1];
+        const int incl = wave_incl_scan(b0 + b1);
+        if (lane == 63) wsum[0][wv] = incl;
+        __syncthreads();
+        int o = incl - b0 - b1;
+        for (int u = 0; u < wv; ++u) o += wsum[0][u];
+        boff[2 * t] = o;
+        boff[2 * t + 1] = o + b0;
+        if (t == 255) boff[kZBuckets] = cnt;
+        __syncthreads();
+#pragma unroll
+        for (int v2 = 0; v2 < kPer; ++v2)
+            if (t + 256 * v2 < cnt)
+                bkey[boff[bk[v2]] + r[v2]] = ((unsigned long long)c[v2].z << 32) | (unsigned)i[v2];
+        // zrow[z]: first charge whose grid z index is >= z
+        for (int z = t; z <= gz; z += 256) zrow[z] = lo + boff[z * m];
+        __syncthreads();
+#pragma unroll
+        for (int v2 = 0; v2 < kPer; ++v2) {
+            if (t + 256 * v2 < cnt) {
+                const unsigned long long mine = ((unsigned long long)c[v2].z << 32) | (unsigned)i[v2];
+                int rank = boff[bk[v2]];
+                const int e = boff[bk[v2] + 1];
+                for (int k = rank, e0 = e; k < e0; ++k) rank += bkey[k] < mine;
+                perm[lo + rank] = i[v2];
+                sorted[lo + rank] = c[v2];
+                skz[rank] = c[v2].z;
             }
-        }
-        for (int k = t; k < cnt; k += 256) {
-            const int p = pay[k];
-            perm[lo + k] = lidx[p];
-            sorted[lo + k] = lrec[p];
-            skz[k] = (uint32_t)(key[k] >> 32);
         }
     } else {
         // rank by counting over the column's segments (O(cnt^2) global reads)
-        for (int k = t; k < cnt; k += 256) {
-            const int sl = slot_of(k);
-            const uint4 c = coord[sl];
-            const int i = slots[sl];
-            const unsigned long long ki = ((unsigned long long)c.z << 32) | (unsigned)i;
-            int rank = 0;
-            for (int bb = 0; bb < nb; ++bb) {
-                const int e = segoff[bb + 1] - segoff[bb];
-                for (int j = 0; j < e; ++j) {
-                    const int sj = segbase[bb] + segoff[bb] + j;
-                    rank += (((unsigned long long)coord[sj].z << 32) | (unsigned)slots[sj]) < ki;
+        for (int b = t; b < nb; b += 256) {
+            const int* rowp = bpre + (size_t)b * stride + col;
+            const int s0 = b * 256 + rowp[0], s1 = b * 256 + rowp[1];
+            for (int sl = s0; sl < s1; ++sl) {
+                const uint4 c = coord[sl];
+                const int i = slots[sl];
+                const unsigned long long ki = ((unsigned long long)c.z << 32) | (unsigned)i;
+                int rank = 0;
+                for (int bb = 0; bb < nb; ++bb) {
+                    const int* rowb = bpre + (size_t)bb * stride + col;
+                    const int e = bb * 256 + rowb[1];
+                    for (int sj = bb * 256 + rowb[0]; sj < e; ++sj)
+                        rank += (((unsigned long long)coord[sj].z << 32) | (unsigned)slots[sj]) < ki;
                 }
+                perm[lo + rank] = i;
+                sorted[lo + rank] = c;
             }
-            perm[lo + rank] = i;
-            sorted[lo + rank] = c;
         }
     }
     __syncthreads();
-    const bool in_lds = cnt <= kSortCap;
-    // z-plane index: zrow[z] = first charge whose grid z index is >= z.  From
-    // the LDS copy, sorted charge k writes the planes after its predecessor's
-    // grid z index up to its own (the last charge also those up to gz);
-    // otherwise a search per plane
-    if (in_lds) {
-        for (int k = t; k < cnt; k += 256) {
-            const int zk = cell_coord(skz[k], gz);
-            const int zp = k > 0 ? cell_coord(skz[k - 1], gz) : -1;
-            for (int z = zp + 1; z <= zk; ++z) zrow[z] = lo + k;
-            if (k == cnt - 1)
-                for (int z = zk + 1; z <= gz; ++z) zrow[z] = lo + cnt;
-        }
-    } else {
+    // z-plane index of a column sorted in global memory: a search per plane
+    if (!in_lds) {
         for (int z = t; z <= gz; z += 256) {
             int l = 0, hh = cnt;
             while (l < hh) {

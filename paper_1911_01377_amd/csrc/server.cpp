@@ -680,7 +680,7 @@ int useries_server_create(useries_server_t* out, size_t hbm_budget_bytes, int ma
     cu = std::max(cu, 1);
     // persistent grids: a few resident blocks per compute unit for each kernel
     S->grid[BK_BINLOCAL] = 4 * cu;
-    S->grid[BK_COLBUILD] = 2 * cu;
+    S->grid[BK_COLBUILD] = 4 * cu;
     S->grid[BK_ENCODE] = 4 * cu;
     S->grid[BK_SCAN] = max_slots;
     S->grid[BK_SCATTER] = 4 * cu;

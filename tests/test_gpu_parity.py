@@ -140,6 +140,31 @@ def test_one_dense_column_global_ranking():
     assert tuple(info["ncell"][:2]) == (4, 4), info["ncell"]
 
 
+@pytest.mark.parametrize("n", [1024, 1025])
+def test_column_at_the_lds_sort_limit(n):
+    """The wire of the test above with 1,024 charges, the most a column sorts
+    in LDS, and with one more."""
+    xyz, q, _ = synth.random_box(n, (3.0, 3.0, 64.0), seed=n)
+    xyz = (xyz + np.array([0.5, 0.5, 0.0], np.float32)).astype(np.float32)
+    compare("wire%d/plain" % n, xyz, q, (20.0, 20.0, 64.0), 9.0, (20, 20, 64), 1e-6, 1e-5,
+            e_scale="parts")
+
+
+@pytest.mark.parametrize("gz", [20, 128])
+def test_columns_of_tied_z(gz):
+    """A 10 x 10 x 10 lattice of alternating unit charges, jittered in x and y
+    only and in shuffled input order: each column's charges share ten values
+    of z, so its sort buckets hold ties that the input index orders."""
+    rng = np.random.default_rng(gz)
+    ijk = np.stack(np.meshgrid(*[np.arange(10)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    xyz = (ijk + 0.5) * 2.0
+    xyz[:, :2] += rng.uniform(-0.4, 0.4, (1000, 2))
+    order = rng.permutation(1000)
+    q = (1.0 - 2.0 * (ijk.sum(1) % 2)).astype(np.float32)[order]
+    compare("ties1000/plain", xyz.astype(np.float32)[order], q, (20.0, 20.0, 20.0), 9.0,
+            (20, 20, gz), 1e-6, 1e-5, e_scale="parts")
+
+
 def test_many_columns_global_binning():
     """A flat 256 x 256 x 19 A cell of 200,000 random charges: 69 x 69
     columns, more than the 4096 whose counts the binning kernels keep in LDS,
