@@ -114,14 +114,13 @@ struct Frag32 {
     f32x4 v[kMaxChunks];
 };
 
-// rows tile*16 + li of the row-major gp x gp matrix m, in the chunk order above
+// row tile `tile` of the gp x gp matrix m (conv_elem_f32), in the chunk order above
 __device__ __forceinline__ void load_frag32(Frag32& f, const float* __restrict__ m, int gp,
-                                            int tile, int li, int lk) {
+                                            int tile, int l) {
+    const float* r = m + (size_t)tile * gp * 16 + 4 * l;
 #pragma unroll
     for (int j = 0; j < kMaxChunks; ++j)
-        if (16 * j < gp)
-            f.v[j] = *reinterpret_cast<const f32x4*>(m + (size_t)(tile * 16 + li) * gp + 16 * j +
-                                                     4 * lk);
+        if (16 * j < gp) f.v[j] = *reinterpret_cast<const f32x4*>(r + j * kFragF32);
 }
 
 __device__ __forceinline__ f32x4 mfma_chunk(f32x4 a, f32x4 b, f32x4 c) {
@@ -152,8 +151,8 @@ __device__ __forceinline__ void conv_xy_f32_body(const ConvArgs& a, int z, int t
     const int ty = w % ty_n, c0 = w / ty_n;      // T = Ky U: row tile, first column strip
     // B of U = rho Kx: Kx[j][k] (Kx symmetric); A of T = Ky U: Ky rows
     Frag32 bx, ay;
-    if (act1) load_frag32(bx, kx + (size_t)p0 * p0 * t, p0, tx, li, lk);
-    if (act2) load_frag32(ay, ky + (size_t)p1 * p1 * t, p1, ty, li, lk);
+    if (act1) load_frag32(bx, kx + (size_t)p0 * p0 * t, p0, tx, l);
+    if (act2) load_frag32(ay, ky + (size_t)p1 * p1 * t, p1, ty, l);
     const float* src = rho + (size_t)z * g1 * g0;
     // octets of the padded plane, two per thread per pass (loads first)
     const int no = p1 * (p0 / 8);
@@ -319,7 +318,7 @@ __device__ __forceinline__ void conv_z_f32_body(const ConvArgs& a, int bid, floa
     auto chunk = [&](int t0) {
         const int nt = (a.nterms - t0 < tc) ? a.nterms - t0 : tc;
         Frag32 cur, nxt;
-        if (act && grp < nt) load_frag32(cur, kz + mz * (t0 + grp), p2, tz, li, lk);
+        if (act && grp < nt) load_frag32(cur, kz + mz * (t0 + grp), p2, tz, l);
         if (t0 > 0) __syncthreads();     // the previous chunk's columns are consumed
         // octets (t, column c, z' = 8 zb .. 8 zb + 7): 8 loads down the
         // column (each coalesced over the 16 columns), two 16-byte stores
@@ -347,7 +346,7 @@ __device__ __forceinline__ void conv_z_f32_body(const ConvArgs& a, int bid, floa
         __syncthreads();
         if (act)
             for (int t = grp; t < nt; t += G) {
-                if (t + G < nt) load_frag32(nxt, kz + mz * (t0 + t + G), p2, tz, li, lk);
+                if (t + G < nt) load_frag32(nxt, kz + mz * (t0 + t + G), p2, tz, l);
                 const float* br = smem + (t * 16 + li) * ld + 4 * lk;
 #pragma unroll
                 for (int j = 0; j < kMaxChunks; ++j)
@@ -368,25 +367,21 @@ __device__ __forceinline__ void conv_z_f32_body(const ConvArgs& a, int bid, floa
 
 // ------------------------------------------------------------------ BF16X3
 
-// kx/ky/kz hold, per term, the hi matrix followed by the lo matrix (bf16 bits).
-//
 constexpr int kMaxKSteps = kMaxGrid / 32;   // K steps of 32 (BF16 MFMA)
 
 struct Frag {
     u16x8 h[kMaxKSteps], l[kMaxKSteps];
 };
 
-// fragment of rows tile*16 + li, k = 32 ks + 8 lk .. + 7, of the gp x gp
-// matrices mh / ml (row-major)
-__device__ __forceinline__ void load_frag(Frag& f, const unsigned short* __restrict__ mh,
-                                          const unsigned short* __restrict__ ml, int gp, int tile,
-                                          int li, int lk) {
+// row tile `tile` of the gp x gp matrix m (conv_elem_bf16)
+__device__ __forceinline__ void load_frag(Frag& f, const unsigned short* __restrict__ m, int gp,
+                                          int tile, int l) {
+    const unsigned short* r = m + (size_t)tile * gp * 32 + 8 * l;
 #pragma unroll
     for (int ks = 0; ks < kMaxKSteps; ++ks) {
         if (32 * ks < gp) {
-            const size_t o = (size_t)(tile * 16 + li) * gp + 32 * ks + 8 * lk;
-            f.h[ks] = *reinterpret_cast<const u16x8*>(mh + o);
-            f.l[ks] = *reinterpret_cast<const u16x8*>(ml + o);
+            f.h[ks] = *reinterpret_cast<const u16x8*>(r + 2 * ks * kFragBf16);
+            f.l[ks] = *reinterpret_cast<const u16x8*>(r + (2 * ks + 1) * kFragBf16);
         }
     }
 }
@@ -412,8 +407,8 @@ __device__ __forceinline__ void conv_xy_bf16_body(const ConvArgs& a, int z, int 
     const int ty = w % ty_n, c0 = w / ty_n;      // T = Ky U: row tile, first column strip
     // B of U = rho Kx: Kx[j][k] (Kx symmetric); A of T = Ky U: Ky rows
     Frag bx, ay;
-    if (act1) load_frag(bx, kx + 2 * mx * t, kx + 2 * mx * t + mx, p0, tx, li, lk);
-    if (act2) load_frag(ay, ky + 2 * my * t, ky + 2 * my * t + my, p1, ty, li, lk);
+    if (act1) load_frag(bx, kx + 2 * mx * t, p0, tx, l);
+    if (act2) load_frag(ay, ky + 2 * my * t, p1, ty, l);
     const float* src = rho + (size_t)z * g1 * g0;
     // octets of the padded plane, two per thread per pass (loads first)
     const int no = p1 * (p0 / 8);
@@ -530,7 +525,7 @@ __device__ __forceinline__ void conv_z_bf16_body(const ConvArgs& a, int bid, flo
         const int nt = (a.nterms - t0 < tc) ? a.nterms - t0 : tc;
         Frag cur, nxt;
         if (act && grp < nt)
-            load_frag(cur, kz + 2 * mz * (t0 + grp), kz + 2 * mz * (t0 + grp) + mz, p2, tz, li, lk);
+            load_frag(cur, kz + 2 * mz * (t0 + grp), p2, tz, l);
         if (t0 > 0) __syncthreads();     // the previous chunk's columns are consumed
         // octets (t, column c, z' = 8 zb .. 8 zb + 7): 8 loads down the
         // column (each coalesced over the 16 columns), one split, two
@@ -561,8 +556,7 @@ __device__ __forceinline__ void conv_z_bf16_body(const ConvArgs& a, int bid, flo
         if (act)
             for (int t = grp; t < nt; t += G) {
                 if (t + G < nt)
-                    load_frag(nxt, kz + 2 * mz * (t0 + t + G), kz + 2 * mz * (t0 + t + G) + mz, p2,
-                              tz, li, lk);
+                    load_frag(nxt, kz + 2 * mz * (t0 + t + G), p2, tz, l);
                 const unsigned short* bhp = th + (t * 16 + li) * ld + 8 * lk;
                 const unsigned short* blp = tl + (t * 16 + li) * ld + 8 * lk;
 #pragma unroll

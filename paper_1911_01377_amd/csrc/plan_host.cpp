@@ -336,7 +336,9 @@ int build_host_plan(HostPlan* hp, const double box[3], double r_c, double b, dou
         ga.dws[a] = (float)(h / (ss * ss));
         const int g = grid[a], gp = ca.gp[a];
         const size_t m = (size_t)gp * gp;
-        // per dense term the circulant M[i][j] = col[(i - j) mod g], zero-padded to gp x gp
+        // per dense term the circulant M[i][j] = col[(i - j) mod g], zero-padded
+        // to gp x gp, in the order in which the matrix-core kernels read it
+        // (conv_elem_*): a wavefront's load of a fragment is then contiguous
         if (bf)
             p.mats[a].assign(2 * m * ca.nterms * sizeof(uint16_t), 0);
         else
@@ -351,18 +353,19 @@ int build_host_plan(HostPlan* hp, const double box[3], double r_c, double b, dou
                 clo[k] = host_bf16(colf[k] - host_bf16_val(chi[k]));
             }
             if (bf) {
-                uint16_t* hi = reinterpret_cast<uint16_t*>(p.mats[a].data()) + 2 * m * t;
-                uint16_t* lo = hi + m;
+                uint16_t* M = reinterpret_cast<uint16_t*>(p.mats[a].data()) + 2 * m * t;
                 for (int i = 0; i < g; ++i)
                     for (int j = 0; j < g; ++j) {
                         const int k = i >= j ? i - j : i - j + g;
-                        hi[(size_t)i * gp + j] = chi[k];
-                        lo[(size_t)i * gp + j] = clo[k];
+                        const size_t e = conv_elem_bf16(gp, i, j);
+                        M[e] = chi[k];
+                        M[e + kFragBf16] = clo[k];
                     }
             } else {
                 float* M = reinterpret_cast<float*>(p.mats[a].data()) + m * t;
                 for (int i = 0; i < g; ++i)
-                    for (int j = 0; j < g; ++j) M[(size_t)i * gp + j] = colf[i >= j ? i - j : i - j + g];
+                    for (int j = 0; j < g; ++j)
+                        M[conv_elem_f32(gp, i, j)] = colf[i >= j ? i - j : i - j + g];
             }
         }
     }
