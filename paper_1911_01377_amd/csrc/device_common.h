@@ -52,6 +52,11 @@ __device__ __forceinline__ int mod_once(int v, int n) {
     return (int)min((uint32_t)v, (uint32_t)(v - n));
 }
 
+// v mod n for 0 <= v < 3n, likewise
+__device__ __forceinline__ int mod_twice(int v, int n) {
+    return (int)min((uint32_t)v, min((uint32_t)(v - n), (uint32_t)(v - 2 * n)));
+}
+
 // floor(v / d) for 0 <= v < 2^25 and 1 < d <= 128, m = magic_of(d): m d exceeds
 // 2^32 by less than d, so v m / 2^32 exceeds v / d by less than v d / (d 2^32)
 // < 1 / 128 <= 1 / d, and the floor is the same

@@ -17,7 +17,24 @@
 
 namespace useries {
 
-// One block of NT threads: thread-strided sums of the pair and far
+// x[t] + x[t + NT] + ... in order, U loads in flight at a time (one at a time,
+// the partials of 210,000 charges took this block 53 memory round trips, as
+// long as the whole gather beside it)
+template <int NT>
+__device__ __forceinline__ double strided_sum(const double* __restrict__ x, int n) {
+    constexpr int U = 8;
+    double s = 0.0;
+    for (int k = threadIdx.x; k < n; k += U * NT) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = k + u * NT < n ? x[k + u * NT] : 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u];
+    }
+    return s;
+}
+
+// One block, its first NT threads: thread-strided sums of the pair and far
 // partials, wavefront sums (DPP), then the NT / 64 wavefront sums in order.
 // wred holds 2 NT / 64 doubles of LDS.
 template <int NT>
@@ -28,11 +45,13 @@ __device__ __forceinline__ void energy_total(const FinalArgs& a, const double* _
                                              double* __restrict__ parts, double* wred) {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     double s = 0.0, g = 0.0;
-    for (int k = t; k < a.n_pair_parts; k += NT) s += pp[k];
-    for (int k = t; k < a.n_far_parts; k += NT) g += fp[k];
+    if (t < NT) {
+        s = strided_sum<NT>(pp, a.n_pair_parts);
+        g = strided_sum<NT>(fp, a.n_far_parts);
+    }
     s = wave_sum_d(s);
     g = wave_sum_d(g);
-    if (lane == 0) {
+    if (lane == 0 && t < NT) {
         wred[2 * w] = s;
         wred[2 * w + 1] = g;
     }

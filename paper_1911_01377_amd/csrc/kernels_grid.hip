@@ -392,19 +392,33 @@ __global__ void __launch_bounds__(64 * kSpreadWaves) k_spread_batch(
 // axis, compiled for that width) or four with 16: a lane owns stencil rows
 // (y, z) and reads the 2P x points of each from LDS; the groups then reduce.
 constexpr int kGatherMaxPieces = 256;     // columns overlapping a brick
-constexpr int kGatherWaves = 8;           // wavefronts per brick
+constexpr int kGatherWaves = 8;           // wavefronts per brick (general stencil)
 constexpr int kGatherThreads = 64 * kGatherWaves;
 constexpr int kGatherBatch = 8;           // halo loads issued together per thread
-constexpr int kGatherOwners = 8;          // owners per wavefront pass, at most
 
 __host__ __device__ constexpr int gather_brick(int P) { return P <= 5 ? 8 : 4; }
+
+// stencil half widths with their own code (the two forms' defaults)
+__host__ __device__ constexpr bool gather_fixed(int P) { return P == 3 || P == 5; }
+// lanes per owner charge
+__host__ __device__ constexpr int gather_lanes(int P) { return P == 3 ? 8 : 16; }
+// Wavefronts of a block: 16 for the P = 5 stencil while the bricks are at most
+// about two per CU (4 passes of a wavefront become 2: 6,600 charges 10.0 -> 8.8
+// us, 26,268 12.2 -> 11.7), beyond that 8, with four blocks per CU (90,180
+// charges 33.2 against 30.0 us).  P = 3: 8 (16 wavefronts 7.1 against 6.6 us at
+// 26,268 charges, 36 against 25 at 210,000).
+constexpr int kGatherWideBricks = 512;
+// owner slots of a block: the candidates of one pass
+__host__ __device__ constexpr int gather_slots(int P) {
+    return gather_fixed(P) ? 256 : kGatherThreads;
+}
 
 // Dynamic LDS of a gather block for stencil half width P (byte offsets): the
 // halo of edge brick + 2P - 1 and the per-owner weights are sized by P.
 struct GatherLds {
     int own, ownf, ownp, sphi, sw, rowtab, pbeg, poff, wtot, total;
 };
-__host__ __device__ inline GatherLds gather_lds(int P) {
+__host__ __device__ constexpr GatherLds gather_lds(int P, int waves) {
     const int E = gather_brick(P) + 2 * P - 1;
     GatherLds L{};
     int o = 0;
@@ -413,23 +427,24 @@ __host__ __device__ inline GatherLds gather_lds(int P) {
         o += (bytes + 15) & ~15;
         return r;
     };
-    L.own = take(16 * kGatherThreads);                 // owner records
-    L.ownf = take(16 * kGatherThreads);                // owners' near forces
-    L.ownp = take(4 * kGatherThreads);                 // owners' input indices
+    L.own = take(16 * gather_slots(P));                // owner records
+    L.ownf = take(16 * gather_slots(P));               // owners' near forces
+    L.ownp = take(4 * gather_slots(P));                // owners' input indices
     L.sphi = take(4 * E * E * E);                      // potential on brick + halo
-    L.sw = take(4 * kGatherWaves * kGatherOwners * 6 * 2 * P);   // weights, derivatives [wave][owner][6][2P]
+    // weights, derivatives [wave][owner][6][2P]
+    L.sw = take(4 * waves * (64 / gather_lanes(P)) * 6 * 2 * P);
     L.rowtab = take(8 * 4 * P * P);                    // stencil rows {offset, ky | kz << 16}
-    L.pbeg = take(4 * kGatherMaxPieces);
-    L.poff = take(4 * (kGatherMaxPieces + 1));
-    L.wtot = take(4 * kGatherWaves);
+    if (!gather_fixed(P)) {
+        L.pbeg = take(4 * kGatherMaxPieces);
+        L.poff = take(4 * (kGatherMaxPieces + 1));
+    }
+    L.wtot = take(4 * waves);
     L.total = o;
     return L;
 }
 
-// PT > 0: the stencil half width as a compile-time constant (fully unrolled
-// stencil rows, weights held in registers); PT = 0 takes it from a.P.
-template <int PT>
-__device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
+// any stencil half width
+__device__ __forceinline__ void gather_any(const GridArgs& a, int bid,
                                             const uint4* __restrict__ sorted,
                                             const int* __restrict__ perm,
                                             const int* __restrict__ zbin,
@@ -437,13 +452,12 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
                                             const float4* __restrict__ fnear,
                                             float* __restrict__ forces, char* lds) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    // LPO lanes per owner charge (8 for a compile-time stencil of at most 8
-    // points per axis, else 16), OPW owners per wavefront pass
-    constexpr int LPO = (PT > 0 && 2 * PT <= 8) ? 8 : 16, OPW = 64 / LPO;
+    // LPO lanes per owner charge, OPW owners per wavefront pass
+    constexpr int LPO = 16, OPW = 64 / LPO;
     const int g = lane / LPO, lg = lane % LPO;
-    const int P = PT > 0 ? PT : a.P, P2 = 2 * P, GB = gather_brick(P);
-    constexpr int KMAX = PT > 0 ? 2 * PT : 2 * kMaxStencilHalf;   // x points per stencil row
-    const GatherLds LL = gather_lds(P);
+    const int P = a.P, P2 = 2 * P, GB = gather_brick(P);
+    constexpr int KMAX = 2 * kMaxStencilHalf;   // x points per stencil row
+    const GatherLds LL = gather_lds(P, kGatherWaves);
     uint4* own = reinterpret_cast<uint4*>(lds + LL.own);
     float4* ownf = reinterpret_cast<float4*>(lds + LL.ownf);
     int* ownp = reinterpret_cast<int*>(lds + LL.ownp);
@@ -477,9 +491,7 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
         zb = zr[Z0];
         ze = zr[Z0 + B2];
     }
-    // the loads of a pass are issued together, then stored; a compile-time
-    // stencil gives a fixed number of passes (unrolled, so the column loads
-    // above stay in flight with the first pass's)
+    // the loads of a pass are issued together, then stored
     auto halo_pass = [&](int base) {
         float v[kGatherBatch];
 #pragma unroll
@@ -499,13 +511,7 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
         }
     };
     constexpr int kPass = kGatherThreads * kGatherBatch;
-    if constexpr (PT > 0) {
-        constexpr int EM = gather_brick(PT) + 2 * PT - 1;   // edge of a whole brick's halo
-#pragma unroll
-        for (int ps = 0; ps < (EM * EM * EM + kPass - 1) / kPass; ++ps) halo_pass(tid + ps * kPass);
-    } else {
-        for (int base = tid; base < nh; base += kPass) halo_pass(base);
-    }
+    for (int base = tid; base < nh; base += kPass) halo_pass(base);
     // stencil rows (ky, kz) of a charge and their offsets in the halo, once per block
     for (int r = tid; r < P2 * P2; r += kGatherThreads) {
         const int ky = r % P2, kz = r / P2;
@@ -566,7 +572,6 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
         }
         __syncthreads();
         // OPW owners per wavefront pass, groups dealt round-robin to the wavefronts
-        static_assert(OPW <= kGatherOwners, "weights sized for kGatherOwners per wavefront");
         for (int o0 = wave * OPW; o0 < nown; o0 += OPW * kGatherWaves) {
             const int o = o0 + g;
             const bool valid = o < nown;
@@ -585,15 +590,15 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
                     for (int ax = 0; ax < 3; ++ax) {
                         const float tt = (float)(lg - P + 1) - f[ax];
                         const float w = a.cw[ax] * __expf(-tt * tt * a.hs[ax]);
-                        swb[((wave * kGatherOwners + g) * 6 + ax) * P2 + lg] = w;
-                        swb[((wave * kGatherOwners + g) * 6 + 3 + ax) * P2 + lg] = w * tt * a.dws[ax];
+                        swb[((wave * OPW + g) * 6 + ax) * P2 + lg] = w;
+                        swb[((wave * OPW + g) * 6 + 3 + ax) * P2 + lg] = w * tt * a.dws[ax];
                     }
                 }
             }
             wave_sync();
             float px = 0.0f, py = 0.0f, pz = 0.0f;
             if (valid) {
-                const float* W = swb + (wave * kGatherOwners + g) * 6 * P2;   // [6][2P]
+                const float* W = swb + (wave * OPW + g) * 6 * P2;   // [6][2P]
                 // stencil point k of the charge is halo point (gi - brick origin) + k
                 const int lx = gi[0] - X0, ly = gi[1] - Y0, lz = gi[2] - Z0;
                 const float* obase = sphi + (lz * E1 + ly) * E0 + lx;
@@ -604,7 +609,7 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
                     float sx = 0.0f, dsx = 0.0f;
 #pragma unroll
                     for (int k = 0; k < KMAX; ++k) {
-                        if (PT > 0 || k < P2) {
+                        if (k < P2) {
                             const float v = rowp[k];
                             sx = fmaf(W[k], v, sx);
                             dsx = fmaf(W[3 * P2 + k], v, dsx);
@@ -616,9 +621,9 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
                     pz = fmaf(wy * W[5 * P2 + kz], sx, pz);
                 }
             }
-            px = LPO == 8 ? sum8(px) : row_sum16(px);
-            py = LPO == 8 ? sum8(py) : row_sum16(py);
-            pz = LPO == 8 ? sum8(pz) : row_sum16(pz);
+            px = row_sum16(px);
+            py = row_sum16(py);
+            pz = row_sum16(pz);
             if (valid && lg == 0) {
                 const float4 fn = ownf[o];    // near force from the pair kernel
                 const int oi = ownp[o];
@@ -632,10 +637,248 @@ __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
     }
 }
 
-// Block xcd_blocks(nb) (one past the bricks' blocks) forms the energy total:
-// it reads only what earlier launches wrote, so it runs beside the bricks.
-template <int PT>
-__global__ void __launch_bounds__(kGatherThreads) k_gather(int nb,
+// The two forms' stencils, P compiled in.  A wavefront evaluates OPW owners at
+// a time, LPO lanes each: the 3 x 2P weights and derivatives are evaluated by
+// the owner's lanes in turn and left in LDS as (weight, derivative) pairs; a
+// lane keeps the x pairs in registers and takes every LPO-th of the (2P)^2
+// stencil rows: 2P potentials from LDS against them, then three products with
+// the row's y and z pairs.
+//
+// Bound: VALU and LDS about evenly: (2P)^3 potentials read and 2 FMAs on each,
+// per charge.  With four weight reads per row, the halo's indices by two
+// divisions per value, a bisection per candidate and 56 KB of LDS (two blocks
+// per CU at P = 5, now 37 KB), 90,180 charges took 42.5 us plain (now 30.0) and
+// 20.3 BF16X3 (14.3); 26,268 charges 14.0 (11.7) and 8.0 (6.7); 210,000 42.2
+// (25.6, of which about 12 by the energy total's loads in flight together).
+template <int P, int kWaves>
+__device__ __forceinline__ void gather_fix(const GridArgs& a, int bid,
+                                           const uint4* __restrict__ sorted,
+                                           const int* __restrict__ perm,
+                                           const int* __restrict__ zbin,
+                                           const float* __restrict__ phi,
+                                           const float4* __restrict__ fnear,
+                                           float* __restrict__ forces, char* lds) {
+    constexpr int P2 = 2 * P, GB = gather_brick(P), E = GB + P2 - 1, R = P2 * P2;
+    constexpr int kSlots = gather_slots(P), kThreads = 64 * kWaves;
+    constexpr int LPO = gather_lanes(P), OPW = 64 / LPO;   // lanes per owner, owners per pass
+    constexpr GatherLds LL = gather_lds(P, kWaves);
+    static_assert(GB == 8 && kSlots % 64 == 0 && kSlots <= kThreads, "");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float4* own = reinterpret_cast<float4*>(lds + LL.own);     // fractions, halo offset
+    float4* ownf = reinterpret_cast<float4*>(lds + LL.ownf);   // near force, charge
+    int* ownp = reinterpret_cast<int*>(lds + LL.ownp);
+    float* sphi = reinterpret_cast<float*>(lds + LL.sphi);
+    int2* rowtab = reinterpret_cast<int2*>(lds + LL.rowtab);
+    int* wtot = reinterpret_cast<int*>(lds + LL.wtot);
+    const Brick K = brick_at(a, bid, GB, a.mb8);
+    // columns overlapping the brick's cells in x and y
+    const int cxl = magic_div(K.o[0] * a.nc[0], a.mg[0]),
+              cxh = magic_div((K.o[0] + K.n[0]) * a.nc[0] + a.g[0] - 1, a.mg[0]) - 1;
+    const int cyl = magic_div(K.o[1] * a.nc[1], a.mg[1]),
+              cyh = magic_div((K.o[1] + K.n[1]) * a.nc[1] + a.g[1] - 1, a.mg[1]) - 1;
+    const int cxn = cxh - cxl + 1, np = cxn * (cyh - cyl + 1);
+    // the charges of the brick's z-planes in columns k0 .. k0 + 63, one per
+    // lane (every wavefront holds them all): loaded first, in flight with the
+    // halo's loads
+    int zb = 0, zn = 0;
+    auto ranges = [&](int k0) {
+        const int k = k0 + lane;
+        zb = zn = 0;
+        if (k < np) {
+            const int ky = small_div(k, __builtin_amdgcn_rcpf((float)cxn));
+            const int* zr = zbin + (size_t)((cyl + ky) * a.nc[0] + cxl + k - ky * cxn) * (a.g[2] + 1);
+            zb = zr[K.o[2]];
+            zn = zr[K.o[2] + K.n[2]] - zb;
+        }
+    };
+    ranges(0);
+    // potential on the brick and halo: local (hx, hy, hz) = global (X0 - P + 1
+    // + hx, ...), E^3 in LDS whatever the brick's own extent.  A thread keeps
+    // its hx and takes every kRows-th row (hy, hz)
+    {
+        constexpr int kRows = kThreads / E, kIter = (E * E + kRows - 1) / kRows;
+        const int r0 = small_div(tid, 1.0f / (float)E), hx = tid - r0 * E;
+        int hz = small_div(r0, 1.0f / (float)E), hy = r0 - hz * E;
+        // origin (modulo the axis) + position < g + E - 1 < 3 g, as g >= 2P
+        static_assert(E - 2 < 2 * P2, "");
+        const int gx = mod_twice(wrap1(K.o[0] - P + 1, a.g[0]) + hx, a.g[0]);
+        const int oy = wrap1(K.o[1] - P + 1, a.g[1]), oz = wrap1(K.o[2] - P + 1, a.g[2]);
+        const bool in = r0 < kRows && hx < K.n[0] + P2 - 1;
+        float v[kIter];
+#pragma unroll
+        for (int u = 0; u < kIter; ++u) {
+            v[u] = 0.0f;
+            if (in && hy < K.n[1] + P2 - 1 && hz < K.n[2] + P2 - 1)
+                v[u] = phi[(size_t)(mod_twice(oz + hz, a.g[2]) * a.g[1] + mod_twice(oy + hy, a.g[1])) *
+                               a.g[0] + gx];
+            hy += kRows % E;
+            hz += kRows / E;
+            if (hy >= E) {
+                hy -= E;
+                ++hz;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kIter; ++u)
+            if (r0 < kRows && r0 + u * kRows < E * E) sphi[(r0 + u * kRows) * E + hx] = v[u];
+    }
+    // stencil rows (ky, kz): offset in the halo, and of the weight pairs (bytes)
+    for (int r = tid; r < R; r += kThreads) {
+        const int kz = small_div(r, 1.0f / (float)P2), ky = r - kz * P2;
+        rowtab[r] = make_int2((kz * E + ky) * E, (P2 + ky) * 8 | ((2 * P2 + kz) * 8) << 16);
+    }
+    // weight evaluations of this lane: values lg, lg + 8, ... of the owner's 6P
+    // (axis, point), and what they take from the axis
+    constexpr int kEval = (3 * P2 + LPO - 1) / LPO;
+    const int g = lane / LPO, lg = lane % LPO;
+    int eax[kEval];
+    float et[kEval], ehs[kEval], ecw[kEval], edw[kEval];
+#pragma unroll
+    for (int m = 0; m < kEval; ++m) {
+        const int i = lg + LPO * m;
+        const int ax = i < P2 ? 0 : i < 2 * P2 ? 1 : 2;
+        eax[m] = ax;
+        et[m] = (float)(i - ax * P2 - P + 1);
+        ehs[m] = ax == 0 ? a.hs[0] : ax == 1 ? a.hs[1] : a.hs[2];
+        ecw[m] = ax == 0 ? a.cw[0] : ax == 1 ? a.cw[1] : a.cw[2];
+        edw[m] = ax == 0 ? a.dws[0] : ax == 1 ? a.dws[1] : a.dws[2];
+    }
+    // this group's weight pairs [axis][point]
+    float2* W = reinterpret_cast<float2*>(lds + LL.sw) + (wave * OPW + g) * 3 * P2;
+
+    for (int k0 = 0; k0 < np; k0 += 64) {
+        if (k0 > 0) ranges(k0);
+        const int incl = wave_incl_scan(zn);
+        const int off = incl - zn, rel = zb - off;
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        for (int base = 0; base < total; base += kSlots) {
+            // candidates base + tid of the ranges laid end to end: the last
+            // range that starts at or before the wavefront's first, then those
+            // that start among them
+            const int t0 = base + 64 * wave, t = t0 + lane;
+            bool mine = false;
+            uint4 c = make_uint4(0, 0, 0, 0);
+            float4 fn = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            int pj = 0;
+            if (wave < kSlots / 64 && t0 < total) {
+                int r = __popcll(__builtin_amdgcn_ballot_w64(off <= t0)) - 1;
+                int j = t + __builtin_amdgcn_readlane(rel, r);
+                for (++r; r < 64; ++r) {
+                    const int o = __builtin_amdgcn_readlane(off, r);
+                    if (o > t0 + 63 || o >= total) break;
+                    if (t >= o) j = t + __builtin_amdgcn_readlane(rel, r);
+                }
+                if (t < total) {
+                    // the near force and input index load with the record (most
+                    // candidates are owners), saving a round trip after the ballot
+                    c = sorted[j];
+                    fn = fnear[j];
+                    pj = perm[j];
+                    const int gx = cell_coord(c.x, a.g[0]), gy = cell_coord(c.y, a.g[1]);
+                    mine = gx >= K.o[0] && gx < K.o[0] + K.n[0] && gy >= K.o[1] &&
+                           gy < K.o[1] + K.n[1];
+                }
+            }
+            const uint64_t m = __builtin_amdgcn_ballot_w64(mine);
+            if (lane == 0) wtot[wave] = __popcll(m);
+            __syncthreads();
+            int before = 0, nown = 0;
+#pragma unroll
+            for (int w = 0; w < kSlots / 64; ++w) {
+                const int n = wtot[w];
+                before += w < wave ? n : 0;
+                nown += n;
+            }
+            nown = __builtin_amdgcn_readfirstlane(nown);
+            if (mine) {
+                const int slot = before + lanes_below(m);
+                int gi[3];
+                float f[3];
+                grid_coord(c.x, a.g[0], &gi[0], &f[0]);
+                grid_coord(c.y, a.g[1], &gi[1], &f[1]);
+                grid_coord(c.z, a.g[2], &gi[2], &f[2]);
+                // stencil point k of the charge is halo point (cell - brick origin) + k
+                const int ob = ((gi[2] - K.o[2]) * E + gi[1] - K.o[1]) * E + gi[0] - K.o[0];
+                own[slot] = make_float4(f[0], f[1], f[2], __int_as_float(ob));
+                ownf[slot] = make_float4(fn.x, fn.y, fn.z, __uint_as_float(c.w));
+                ownp[slot] = pj;
+            }
+            __syncthreads();
+            // OPW owners per wavefront pass, groups dealt round-robin to the wavefronts
+            for (int o0 = wave * OPW; o0 < nown; o0 += OPW * kWaves) {
+                const int o = min(o0 + g, nown - 1);     // a group past the end repeats the last
+                const float* of = reinterpret_cast<const float*>(own + o);
+#pragma unroll
+                for (int v = 0; v < kEval; ++v) {
+                    const float tt = et[v] - of[eax[v]];
+                    const float w = ecw[v] * __expf(-tt * tt * ehs[v]);
+                    if (LPO * (v + 1) <= 3 * P2 || lg + LPO * v < 3 * P2)
+                        W[lg + LPO * v] = make_float2(w, w * tt * edw[v]);
+                }
+                const float* obase = sphi + __float_as_int(of[3]);
+                wave_sync();
+                float2 wx[P2];
+#pragma unroll
+                for (int k = 0; k < P2; ++k) wx[k] = W[k];
+                float px = 0.0f, py = 0.0f, pz = 0.0f;
+#pragma unroll
+                for (int it = 0; it < (R + LPO - 1) / LPO; ++it) {
+                    if (LPO * (it + 1) <= R || lg + LPO * it < R) {
+                        const int2 rt = rowtab[lg + LPO * it];
+                        const float* rowp = obase + rt.x;
+                        const float2 wy = *reinterpret_cast<const float2*>(
+                            reinterpret_cast<const char*>(W) + (rt.y & 0xffff));
+                        const float2 wz = *reinterpret_cast<const float2*>(
+                            reinterpret_cast<const char*>(W) + (rt.y >> 16));
+                        float sx = 0.0f, dsx = 0.0f;
+#pragma unroll
+                        for (int k = 0; k < P2; ++k) {
+                            const float v = rowp[k];
+                            sx = fmaf(wx[k].x, v, sx);
+                            dsx = fmaf(wx[k].y, v, dsx);
+                        }
+                        px = fmaf(wy.x * wz.x, dsx, px);
+                        py = fmaf(wy.y * wz.x, sx, py);
+                        pz = fmaf(wy.x * wz.y, sx, pz);
+                    }
+                }
+                px = LPO == 8 ? sum8(px) : row_sum16(px);
+                py = LPO == 8 ? sum8(py) : row_sum16(py);
+                pz = LPO == 8 ? sum8(pz) : row_sum16(pz);
+                if (lg == 0 && o0 + g < nown) {
+                    const float4 fo = ownf[o];    // near force from the pair kernel, charge
+                    float* out = forces + 3 * (size_t)ownp[o];
+                    out[0] = fo.x - fo.w * px;
+                    out[1] = fo.y - fo.w * py;
+                    out[2] = fo.z - fo.w * pz;
+                }
+                wave_sync();
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// PT = 3 or 5, or 0: a.P, any (NW = kGatherWaves)
+template <int PT, int NW>
+__device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
+                                            const uint4* __restrict__ sorted,
+                                            const int* __restrict__ perm,
+                                            const int* __restrict__ zbin,
+                                            const float* __restrict__ phi,
+                                            const float4* __restrict__ fnear,
+                                            float* __restrict__ forces, char* lds) {
+    if constexpr (PT > 0)
+        gather_fix<PT, NW>(a, bid, sorted, perm, zbin, phi, fnear, forces, lds);
+    else
+        gather_any(a, bid, sorted, perm, zbin, phi, fnear, forces, lds);
+}
+
+// Block 0 forms the energy total: it reads only what earlier launches wrote, so
+// it runs beside the bricks (first, as it has the longest chain of loads).
+template <int PT, int NW>
+__global__ void __launch_bounds__(64 * NW) k_gather(int nb,
                                                 const int* __restrict__ zbin,
                                                 const float* __restrict__ phi,
                                                 const uint4* __restrict__ sorted,
@@ -649,13 +892,13 @@ __global__ void __launch_bounds__(kGatherThreads) k_gather(int nb,
                                                 double* __restrict__ parts, GridArgs a,
                                                 FinalArgs fa) {
     extern __shared__ char dyn[];
-    if ((int)blockIdx.x == xcd_blocks(nb)) {
+    if (blockIdx.x == 0) {
         energy_total<kGatherThreads>(fa, pair_parts, far_parts, qstats, energy, parts,
                                      reinterpret_cast<double*>(dyn));
         return;
     }
-    const int item = xcd_item(blockIdx.x, nb);
-    if (item < nb) gather_body<PT>(a, item, sorted, perm, zbin, phi, fnear, forces, dyn);
+    const int item = xcd_item(blockIdx.x - 1, nb);
+    if (item < nb) gather_body<PT, NW>(a, item, sorted, perm, zbin, phi, fnear, forces, dyn);
 }
 
 // PT > 0 only when every box of the batch has stencil half width PT
@@ -670,7 +913,7 @@ __global__ void __launch_bounds__(kGatherThreads) k_gather_batch(const BatchTabl
                                          d.energies + tab->step[i], nullptr,
                                          reinterpret_cast<double*>(dyn));
         else
-            gather_body<PT>(d.grid, item, d.sorted, d.perm, d.zbin, d.phi, d.fnear, d.forces,
+            gather_body<PT, kGatherWaves>(d.grid, item, d.sorted, d.perm, d.zbin, d.phi, d.fnear, d.forces,
                             dyn);
     });
 }
@@ -694,18 +937,20 @@ hipError_t launch_gather(const GridArgs& a, const uint4* sorted, const int* perm
                          const FinalArgs& fa, const double* pair_parts, const double* far_parts,
                          const double* qstats, double* energy, double* parts, hipStream_t st) {
     const int nb = gather_blocks(a);
-    const dim3 grid(xcd_blocks(nb) + 1), block(kGatherThreads);
-    const size_t lds = gather_lds(a.P).total;
+    const dim3 grid(xcd_blocks(nb) + 1);
     // the default stencils of the two forms (P = 3, 5) have their own code
-#define USERIES_GATHER_LAUNCH(PT)                                                            \
-    hipLaunchKernelGGL(k_gather<PT>, grid, block, lds, st, nb, zbin, phi, sorted, fnear,     \
+#define USERIES_GATHER_LAUNCH(PT, NW)                                                        \
+    hipLaunchKernelGGL((k_gather<PT, NW>), grid, dim3(64 * NW),                              \
+                       (size_t)gather_lds(a.P, NW).total, st, nb, zbin, phi, sorted, fnear,  \
                        perm, forces, pair_parts, far_parts, qstats, energy, parts, a, fa)
     if (a.P == 3)
-        USERIES_GATHER_LAUNCH(3);
+        USERIES_GATHER_LAUNCH(3, kGatherWaves);
+    else if (a.P == 5 && nb <= kGatherWideBricks)
+        USERIES_GATHER_LAUNCH(5, 16);
     else if (a.P == 5)
-        USERIES_GATHER_LAUNCH(5);
+        USERIES_GATHER_LAUNCH(5, kGatherWaves);
     else
-        USERIES_GATHER_LAUNCH(0);
+        USERIES_GATHER_LAUNCH(0, kGatherWaves);
 #undef USERIES_GATHER_LAUNCH
     return hipGetLastError();
 }
@@ -716,7 +961,7 @@ hipError_t launch_spread_batch(const BatchTable* tab, const BoxDesc* desc, int g
     return hipGetLastError();
 }
 
-size_t gather_lds_bytes(int P) { return (size_t)gather_lds(P).total; }
+size_t gather_lds_bytes(int P) { return (size_t)gather_lds(P, kGatherWaves).total; }
 
 hipError_t launch_gather_batch(const BatchTable* tab, const BoxDesc* desc, int P, size_t lds,
                                int grid, hipStream_t st) {

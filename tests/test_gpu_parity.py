@@ -194,6 +194,37 @@ def test_many_columns_global_binning():
     assert fsum <= 1e-3 * math.sqrt(len(q)) * rms
 
 
+def test_more_than_64_columns_under_a_brick():
+    """A jittered 32^3 lattice of alternating unit charges in an 18 A cell on a
+    14^3 grid (BF16X3): 15 x 15 columns, so a gather brick overlaps 81 of them
+    (the ranges are held 64 at a time) and a spreading brick's window all 225.
+    Forces on 128 sampled charges."""
+    rng = np.random.default_rng(71)
+    ijk = np.stack(np.meshgrid(*[np.arange(32)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    xyz = ((ijk + 0.5) * (18.0 / 32) + rng.uniform(-0.1, 0.1, ijk.shape)).astype(np.float32)
+    q = (1.0 - 2.0 * (ijk.sum(1) % 2)).astype(np.float32)
+    box, rc = (18.0, 18.0, 18.0), 4.7
+    _, gf, info = gpu_eval(xyz, q, box, rc, (14, 14, 14), precision=USERIES_BF16X3)
+    assert tuple(info["ncell"][:2]) == (15, 15), info["ncell"]
+    idx = rng.choice(len(q), 128, replace=False)
+    fo = oracle.forces_subset(xyz.astype(np.float64), q.astype(np.float64), box,
+                              oracle_params(info, rc), idx)
+    df = rel_rms(gf[idx], fo)
+    log("case columns under a brick/bf16x3: dF(128 sampled)=%.2e" % df)
+    assert df <= 1e-3
+
+
+@pytest.mark.parametrize("nx,nz", [(8, 8), (9, 8)])
+def test_gather_on_either_side_of_512_bricks(nx, nz):
+    """512 bricks (16 wavefronts per gather block at P = 5) and 576 (8), on a
+    32 A cell of water, against a 48^3 grid (216 bricks): the forces agree to
+    the sum of the grids' own errors (1e-5 each)."""
+    xyz, q, box = synth.water_box(n_mol=1094, L=32.0, seed=9)
+    _, f, _ = gpu_eval(xyz, q, box, 9.0, (8 * nx, 64, 8 * nz))
+    _, f0, _ = gpu_eval(xyz, q, box, 9.0, (48, 48, 48))
+    assert rel_rms(f, f0) <= 2e-5
+
+
 FORMS = [(0, (1e-6, 1e-5)), (USERIES_BF16X3, (1e-3, 1e-3))]
 
 
