@@ -193,8 +193,10 @@ int build_host_plan(HostPlan* hp, const double box[3], double r_c, double b, dou
         const double is2 = 1.0 / (ux * ux);
         pa.is2h = (float)is2;
         pa.is2l = (float)(is2 - (double)pa.is2h);
-        const float rcm = std::sqrt(pa.rc2) + 1e-3f;
-        pa.rcm2 = rcm * rcm;
+        const double lmax = std::max({box[0], box[1], box[2]});
+        const double rcm = (r_c + 1e-3) / lmax;
+        pa.rcm2 = (float)(rcm * rcm);
+        for (int a = 0; a < 3; ++a) pa.edge[a] = (float)(box[a] / 4294967296.0 / lmax);
     }
 
     // far part.  A term so wide that every non-zero Fourier mode of its

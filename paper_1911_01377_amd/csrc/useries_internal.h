@@ -79,7 +79,8 @@ struct PairArgs {
     float inv_scale;      // 1 / scale[0] (FP32)
     double inv_scale_d;   // 1 / scale[0] (FP64)
     float is2h, is2l;     // (1 / (scale[0] + scale_lo[0]))^2 as FP32 hi + lo
-    float rcm2;           // (r_c + 1e-3)^2: the bounding-box test's reach
+    float edge[3];        // scale / longest edge: fixed-point units to longest edges
+    float rcm2;           // ((r_c + 1e-3) / longest edge)^2: the bounding-box test's reach
     float cw[2];          // column widths L / nc
     float zinv;           // 2^32 / L_z: A to fixed-point units along z
     float rc2;            // r_c^2
