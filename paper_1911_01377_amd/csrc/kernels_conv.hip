@@ -19,6 +19,8 @@
 // A[l % 16][k] and B[k][l % 16], with k = l / 16 (16x16x4 f32) or
 // k = 8 (l / 16) + 0..7 (16x16x32 bf16); it receives D[4 (l / 16) + r][l % 16],
 // r = 0..3.
+#include <algorithm>
+
 #include "useries_internal.h"
 #include "device_common.h"
 
@@ -580,6 +582,104 @@ __device__ __forceinline__ void conv_z_bf16_body(const ConvArgs& a, int bid, flo
     conv_z_store(a, bid, tz, li, lk, c0, acc, ps, rv, phi, fpart);
 }
 
+// The same on grids of many columns: kWideTiles tiles of 16 columns per block
+// share the Kz fragments; the columns of a chunk of terms (one staging octet per
+// thread, a multiple of the groups) go through two LDS buffers by turns, and the
+// next chunk's columns and Kz fragments load during the products: one barrier
+// per chunk.  128^3 points 30.6 -> 22.7 us, 100 x 100 x 90 16.9 -> 15.4; with
+// fewer blocks than two per CU the halved parallelism costs more (64^3 5.8 ->
+// 7.5), and FP32, bound by its matrix instructions, is slower too (100 x 100 x
+// 90 23.7 -> 25.2).
+constexpr int kWideTiles = 2;
+constexpr int kWideBlocks = 512;   // blocks of 16 columns from which it is taken
+__host__ __device__ inline int conv_z_wide_chunk(const ConvArgs& a) {
+    const int G = conv_z_groups(a), tc = kConvThreads / (16 * kWideTiles * (a.gp[2] / 8));
+    return tc > G ? tc - tc % G : G;
+}
+
+__device__ __forceinline__ void conv_z_bf16_wide(const ConvArgs& a, int bid, float* smem,
+                                                const float* __restrict__ tgrid,
+                                                const unsigned short* __restrict__ kz,
+                                                float* __restrict__ phi,
+                                                const float* __restrict__ rho,
+                                                double* __restrict__ fpart) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int li = l & 15, lk = l >> 4;
+    const int g2 = a.g[2], p2 = a.gp[2], ld = p2 + 8;
+    const int ncol = a.g[0] * a.g[1];
+    const int tz_n = p2 / 16, G = conv_z_groups(a);
+    const int cb = bid * 16 * kWideTiles;
+    const int grp = small_div(w, __builtin_amdgcn_rcpf((float)tz_n)), tz = w - grp * tz_n;
+    const bool act = grp < G;
+    const size_t mz = (size_t)p2 * p2;
+    const int tc = conv_z_wide_chunk(a), nchunk = (a.nterms + tc - 1) / tc;
+    const int part = tc * 16 * kWideTiles * ld;          // one buffer's hi or lo part
+    unsigned short* sm = reinterpret_cast<unsigned short*>(smem);
+    // this thread's octet of a chunk: term t, column c, z' = 8 zb .. 8 zb + 7
+    const int c = threadIdx.x % (16 * kWideTiles), q8 = threadIdx.x / (16 * kWideTiles);
+    const int ot = small_div(q8, __builtin_amdgcn_rcpf((float)(p2 / 8))), zb = q8 - ot * (p2 / 8);
+    const bool oin = ot < tc;
+    const bool cin = cb + c < ncol;
+    auto load = [&](int k, float v[8]) {
+        const int t = k * tc + ot;
+        const float* src = tgrid + ((size_t)t * g2 + 8 * zb) * ncol + cb + c;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v[u] = oin && t < a.nterms && cin && 8 * zb + u < g2 ? src[(size_t)u * ncol] : 0.0f;
+    };
+    auto store = [&](int k, const float v[8]) {
+        if (!oin) return;
+        u16x8 h, lo;
+        split8(v, &h, &lo);
+        unsigned short* d = sm + (k & 1) * 2 * part + (ot * 16 * kWideTiles + c) * ld + 8 * zb;
+        *reinterpret_cast<u16x8*>(d) = h;
+        *reinterpret_cast<u16x8*>(d + part) = lo;
+    };
+    float v[8];
+    load(0, v);
+    Frag cur, nxt;
+    if (act && grp < a.nterms) load_frag(cur, kz + 2 * mz * grp, p2, tz, l);
+    f32x4 rv[kWideTiles], acc[kWideTiles];
+#pragma unroll
+    for (int n = 0; n < kWideTiles; ++n) {
+        rv[n] = act && grp == 0 ? conv_z_rho(a, tz, li, lk, cb + 16 * n, rho)
+                                : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        acc[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    store(0, v);
+    __syncthreads();
+    for (int k = 0; k < nchunk; ++k) {
+        if (k + 1 < nchunk) load(k + 1, v);
+        if (act)
+            for (int t = grp; t < tc && k * tc + t < a.nterms; t += G) {
+                // the wavefront's next term: its next of this chunk or (tc is a
+                // multiple of G) its first of the next one
+                if (k * tc + t + G < a.nterms) load_frag(nxt, kz + 2 * mz * (k * tc + t + G), p2, tz, l);
+                const unsigned short* br = sm + (k & 1) * 2 * part + (t * 16 * kWideTiles + li) * ld + 8 * lk;
+#pragma unroll
+                for (int ks = 0; ks < kMaxKSteps; ++ks)
+                    if (32 * ks < p2)
+#pragma unroll
+                        for (int n = 0; n < kWideTiles; ++n) {
+                            const unsigned short* b = br + n * 16 * ld + 32 * ks;
+                            acc[n] = mfma3(cur.h[ks], cur.l[ks], *reinterpret_cast<const u16x8*>(b),
+                                           *reinterpret_cast<const u16x8*>(b + part), acc[n]);
+                        }
+                cur = nxt;
+            }
+        if (k + 1 < nchunk) store(k + 1, v);
+        __syncthreads();
+    }
+    if (G > 1)
+#pragma unroll
+        for (int n = 0; n < kWideTiles; ++n) acc[n] = conv_z_reduce(acc[n], smem, act, grp, G, tz, tz_n, l);
+    if (!act || grp != 0) return;
+#pragma unroll
+    for (int n = 0; n < kWideTiles; ++n)
+        if (cb + 16 * n < ncol)
+            conv_z_store(a, bid * kWideTiles + n, tz, li, lk, cb + 16 * n, acc[n], nullptr, rv[n], phi, fpart);
+}
+
 // ------------------------------------------------------------------ spectral wide terms
 // The widest terms together as (U_z x U_y x U_x) diag(W) (U_z x U_y x U_x)^T rho
 // (ConvArgs::spec), in three steps, FP32 FMAs (a few hundred thousand per
@@ -787,6 +887,16 @@ __global__ void __launch_bounds__(kConvThreads) k_conv_z_bf16(int nb, int spec_o
     conv_z_bf16_body(a, item, dyn_lds, tgrid, kz, phi, rho, fpart, ps);
 }
 
+// conv_z of many columns (BF16X3, no spectral terms)
+__global__ void __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(4)))
+k_conv_z_bf16_wide(int nb, const float* __restrict__ tgrid,
+                   const unsigned short* __restrict__ kz, float* __restrict__ phi,
+                   const float* __restrict__ rho, double* __restrict__ fpart, ConvArgs a) {
+    extern __shared__ float dyn_lds[];
+    const int item = xcd_item(blockIdx.x, nb);
+    if (item < nb) conv_z_bf16_wide(a, item, dyn_lds, tgrid, kz, phi, rho, fpart);
+}
+
 // batched: item = t * g_z + z (conv_xy), 16-column group (conv_z)
 template <int BF16>
 __global__ void __launch_bounds__(kConvThreads) k_conv_xy_batch(const BatchTable* __restrict__ tab,
@@ -877,6 +987,16 @@ hipError_t launch_conv_z(const ConvArgs& a, const float* tgrid, const float* kz,
         const int n = a.rk[2] * a.rk[1] * a.rk[0];
         hipLaunchKernelGGL(k_spec_core, dim3((n + 15) / 16), dim3(kSpecCoreThreads), 0, st, g, a,
                            sp);
+    }
+    if (a.bf16x3 && !a.spec && nb >= kWideBlocks) {
+        const int nbw = (nb + kWideTiles - 1) / kWideTiles;
+        const size_t stage =
+            (size_t)2 * conv_z_wide_chunk(a) * 16 * kWideTiles * (a.gp[2] + 8) * 4;
+        const size_t red = (size_t)(conv_z_groups(a) - 1) * (a.gp[2] / 16) * 64 * 4 * sizeof(float);
+        hipLaunchKernelGGL(k_conv_z_bf16_wide, dim3(xcd_blocks(nbw)), dim3(kConvThreads),
+                           std::max(stage, red), st, nbw, tgrid,
+                           reinterpret_cast<const unsigned short*>(kz), phi, rho, fpart, a);
+        return hipGetLastError();
     }
     const int off = (int)(conv_z_dense_lds_bytes(a) / sizeof(float));
     if (a.bf16x3)

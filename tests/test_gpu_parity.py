@@ -214,6 +214,19 @@ def test_more_than_64_columns_under_a_brick():
     assert df <= 1e-3
 
 
+@pytest.mark.parametrize("grid", [(90, 91, 64), (91, 90, 30), (96, 86, 31), (91, 90, 110)])
+def test_wide_z_convolution(grid):
+    """BF16X3 grids of 8,190 to 8,256 (x, y) columns: 512 groups of 16 and
+    more, from which conv_z takes two groups per block, ragged last ones among
+    them; padded z lengths of 32, 64 and 128 (4, 2 and 1 term groups).  Against
+    a grid below the line (44 x 44) on the same cell: the forces agree to the
+    sum of the grids' own errors (1e-3 each)."""
+    xyz, q, box = synth.water_box(n_mol=1094, L=32.0, seed=12)
+    _, f, _ = gpu_eval(xyz, q, box, 9.0, grid, precision=USERIES_BF16X3)
+    _, f0, _ = gpu_eval(xyz, q, box, 9.0, (44, 44, grid[2]), precision=USERIES_BF16X3)
+    assert rel_rms(f, f0) <= 2e-3
+
+
 @pytest.mark.parametrize("nx,nz", [(8, 8), (9, 8)])
 def test_gather_on_either_side_of_512_bricks(nx, nz):
     """512 bricks (16 wavefronts per gather block at P = 5) and 576 (8), on a
