@@ -249,9 +249,10 @@ struct useries_server_s {
     // the kernels of one step, in order, on the server stream
     // P: the stencil half width shared by the step's boxes, 0 if they differ;
     // exact: the most leading far terms a box evaluates as Gaussians in its near part;
-    // bins: bit 0 some box bins in two launches, bit 1 some box in four
+    // bins: bit 0 some box bins in two launches, bit 1 some box in four;
+    // grid: blocks per kernel
     hipError_t enqueue_kernels(size_t lds, size_t lds_z, size_t lds_g, int P, int exact,
-                               int bins) {
+                               int bins, const int* grid) {
         const bool bf = precision == USERIES_BF16X3;
         hipError_t e;
         if ((bins & 1) && (e = launch_bin_local_batch(d_table, d_desc, grid[BK_BINLOCAL], st)))
@@ -283,7 +284,7 @@ struct useries_server_s {
         }
         hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
         if (e) return e;
-        const hipError_t el = enqueue_kernels(lds, lds_z, lds_g, P, exact, bins);
+        const hipError_t el = enqueue_kernels(lds, lds_z, lds_g, P, exact, bins, grid);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(st, &g);
         if (el) {
@@ -453,8 +454,17 @@ struct useries_server_s {
             hipGraphExec_t ex = nullptr;
             if ((e = graph_for(lds, lds_z, lds_g, P, exact, bins, &ex))) return e;
             if ((e = hipGraphLaunch(ex, st))) return e;
-        } else if ((e = enqueue_kernels(lds, lds_z, lds_g, P, exact, bins))) {
-            return e;
+        } else {
+            // a step launched by itself takes a block per item: blocks then leave
+            // as they end and others start, where a persistent block waits at
+            // each item's first loads (20 cells: pair 119 -> 100 us a step, spread
+            // 44 -> 35, the group of ten evaluations 5.75 -> 5.2 ms).  Gather
+            // alone is as fast persistent (33.9 against 35.4 us).  A captured
+            // step serves every batch, so its grids stay fixed
+            int gs[BK_COUNT];
+            for (int k = 0; k < BK_COUNT; ++k)
+                gs[k] = k == BK_GATHER ? grid[k] : std::max(1, T.off[k][nb]);
+            if ((e = enqueue_kernels(lds, lds_z, lds_g, P, exact, bins, gs))) return e;
         }
         if ((e = hipEventRecord(ring_ev[r], st))) return e;
         ring_used[r] = true;
