@@ -636,15 +636,18 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
     for (int u = 0; u < wv; ++u) off += wsum[0][u];
     const int cnt = ((wsum[0][0] + wsum[0][1]) + wsum[0][2]) + wsum[0][3];
     const int lo = ((wsum[1][0] + wsum[1][1]) + wsum[1][2]) + wsum[1][3];
-    // list position off + j of segment b holds record 256 b + P[b][c] + j
-    if (cnt <= kSortCap) {
+    // list position off + j of segment b holds record 256 b + P[b][c] + j; of
+    // a column too long for that the segments' bounds, where they fit
+    int2* const seg = reinterpret_cast<int2*>(bkey);
+    const bool segs = cnt > kSortCap && nb <= kSortCap;
 #pragma unroll
-        for (int u = 0; u < kLocalRun; ++u) {
-            if (blo + u < bhi) {
-                const int r0 = (blo + u) * 256 + pc[u];
+    for (int u = 0; u < kLocalRun; ++u) {
+        if (blo + u < bhi) {
+            const int r0 = (blo + u) * 256 + pc[u];
+            if (segs) seg[blo + u] = make_int2(r0, r0 + h[u]);
+            if (cnt <= kSortCap)
                 for (int j = 0; j < h[u]; ++j) lslot[off + j] = r0 + j;
-                off += h[u];
-            }
+            off += h[u];
         }
     }
     if (reduce_q && wv == 1) qstats_reduce(nb, qpart, qstats);
@@ -713,18 +716,21 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
         }
     } else {
         // rank by counting over the column's segments (O(cnt^2) global reads)
-        for (int b = t; b < nb; b += 256) {
+        auto bounds = [&](int b) {
+            if (segs) return seg[b];
             const int* rowp = bpre + (size_t)b * stride + col;
-            const int s0 = b * 256 + rowp[0], s1 = b * 256 + rowp[1];
-            for (int sl = s0; sl < s1; ++sl) {
+            return make_int2(b * 256 + rowp[0], b * 256 + rowp[1]);
+        };
+        for (int b = t; b < nb; b += 256) {
+            const int2 sb = bounds(b);
+            for (int sl = sb.x; sl < sb.y; ++sl) {
                 const uint4 c = coord[sl];
                 const int i = slots[sl];
                 const unsigned long long ki = ((unsigned long long)c.z << 32) | (unsigned)i;
                 int rank = 0;
                 for (int bb = 0; bb < nb; ++bb) {
-                    const int* rowb = bpre + (size_t)bb * stride + col;
-                    const int e = bb * 256 + rowb[1];
-                    for (int sj = bb * 256 + rowb[0]; sj < e; ++sj)
+                    const int2 o = bounds(bb);
+                    for (int sj = o.x; sj < o.y; ++sj)
                         rank += (((unsigned long long)coord[sj].z << 32) | (unsigned)slots[sj]) < ki;
                 }
                 perm[lo + rank] = i;

@@ -150,6 +150,26 @@ def test_column_at_the_lds_sort_limit(n):
             e_scale="parts")
 
 
+def test_dense_column_among_many_blocks():
+    """262,500 random charges in a 140 A cube and 1,500 more in a 3 x 3 A wire
+    along z: a column of more than 1,024 charges, ranked from global memory,
+    whose 1,032 blocks of 256 input charges do not fit the table of segment
+    bounds.  Forces on 64 sampled charges of the wire."""
+    x1, q1, _ = synth.random_box(262500, (140.0, 140.0, 140.0), seed=81)
+    x2, q2, _ = synth.random_box(1500, (3.0, 3.0, 140.0), seed=82)
+    xyz = np.concatenate([x1, x2 + np.array([0.3, 0.3, 0.0], np.float32)]).astype(np.float32)
+    q, box, rc = np.concatenate([q1, q2]), (140.0, 140.0, 140.0), 9.0
+    order = np.random.default_rng(83).permutation(len(q))
+    xyz, q = xyz[order], q[order]
+    _, gf, info = gpu_eval(xyz, q, box, rc, (128, 128, 128))
+    idx = np.nonzero(order >= 262500)[0][:64]
+    fo = oracle.forces_subset(xyz.astype(np.float64), q.astype(np.float64), box,
+                              oracle_params(info, rc), idx)
+    df = rel_rms(gf[idx], fo)
+    log("case dense column among many blocks/plain: dF(64 sampled)=%.2e" % df)
+    assert df <= 1e-5
+
+
 @pytest.mark.parametrize("gz", [20, 128])
 def test_columns_of_tied_z(gz):
     """A 10 x 10 x 10 lattice of alternating unit charges, jittered in x and y
