@@ -170,6 +170,55 @@ def test_dense_column_among_many_blocks():
     assert df <= 1e-5
 
 
+def kernel_us(xyz, q, box, rc, grid, kernel, reps=5, **kw):
+    """Mean time of one kernel of an evaluation, after a first one."""
+    from paper_1911_01377_amd import Plan
+    plan = Plan(box, rc, grid, **kw)
+    x, qq = torch.from_numpy(xyz).cuda(), torch.from_numpy(q).cuda()
+    plan.eval(x, qq)
+    plan.timing(True)
+    for _ in range(reps):
+        plan.eval(x, qq)
+    torch.cuda.synchronize()
+    ms = {name: total / max(count, 1) for name, total, count in plan.timing()}
+    plan.close()
+    return 1e3 * ms[kernel]
+
+
+def wire(n, seed):
+    """n charges +-1 in a 3 x 3 A wire along z of a 20 x 20 x 64 A cell (one
+    column holds them all), no two at the same z, in increasing z."""
+    rng = np.random.default_rng(seed)
+    xyz = np.empty((n, 3), np.float32)
+    xyz[:, :2] = rng.uniform(0.5, 3.5, (n, 2))
+    xyz[:, 2] = (np.arange(n) + rng.uniform(0.0, 0.5, n)) * (64.0 / n)
+    return xyz, rng.choice([-1.0, 1.0], n).astype(np.float32), (20.0, 20.0, 64.0)
+
+
+@pytest.mark.parametrize("n", [1025, 2048, 2049, 4100])
+def test_long_column_in_any_input_order(n):
+    """A column longer than the LDS sort, its charges in z order (few input
+    blocks per stretch of it) and shuffled: it sorts to the same sequence, so
+    the forces are the same bits."""
+    xyz, q, box = wire(n, n)
+    order = np.random.default_rng(n).permutation(n)
+    _, f0, _ = gpu_eval(xyz, q, box, 9.0, (20, 20, 64))
+    _, f1, _ = gpu_eval(xyz[order], q[order], box, 9.0, (20, 20, 64))
+    assert np.array_equal(f0[order], f1)
+
+
+@pytest.mark.parametrize("n", [1100, 2000])
+def test_long_column_uses_all_threads(n):
+    """Sorting a column of 1,100 or 2,000 charges, which lie in 5 or 8 blocks
+    of 256 input charges, takes at most 100 times as long as one of 1,000 in
+    LDS.  (Four to eight charges per thread against n keys from global memory
+    are 35 to 100 times, one thread per input block was 1,600 to 3,000.)"""
+    short = kernel_us(*wire(1000, 1), 9.0, (20, 20, 64), "colbuild")
+    long = kernel_us(*wire(n, 2), 9.0, (20, 20, 64), "colbuild")
+    log("case wire%d: colbuild %.1f us, 1,000 charges %.1f us" % (n, long, short))
+    assert long <= 100.0 * short
+
+
 @pytest.mark.parametrize("gz", [20, 128])
 def test_columns_of_tied_z(gz):
     """A 10 x 10 x 10 lattice of alternating unit charges, jittered in x and y
