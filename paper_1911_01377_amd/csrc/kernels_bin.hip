@@ -564,7 +564,12 @@ __device__ __forceinline__ void bin_local_body(const BinArgs& a, int b, const fl
 // index and clusters.  Up to kSortCap charges are sorted by z buckets in LDS
 // (a whole number of buckets per grid plane, about 512 in all): a charge's
 // rank is its bucket's offset plus the keys of its bucket below its own, and
-// the offsets at the planes are the z-plane index.  Of longer columns kSortCap
+// the offsets at the planes are the z-plane index.  A bucket of more than an
+// eighth of the column (charges at a few values of z, as in a crystal's or an
+// electrode's planes) makes it count against all of the column's keys: those
+// reads are the same for every thread, so several are in flight, at 5 to 9 ns per
+// key and charge of a thread against 46 for the bucket's own, one after another
+// (a column at one z: 256 charges 21 -> 13 us, 1,024 202 -> 49).  Of longer columns kSortCap
 // charges at a time, four per thread, are ranked against the whole column, whose
 // keys pass through LDS in tiles of kSortCap.  Every list position has its thread
 // whichever input blocks hold it: dealing the blocks' segments to the threads
@@ -595,10 +600,10 @@ __device__ __forceinline__ void qstats_reduce(int nb, const double* __restrict__
     }
 }
 
-// rank += how many of the m keys in LDS lie below the thread's own
+// rank += how many of the m keys in LDS lie below each of the thread's own N
 template <int N>
 __device__ __forceinline__ void rank_among(const unsigned long long* key, int m,
-                                           const unsigned long long (&mine)[N], int (&rank)[N]) {
+                                           const unsigned long long* mine, int* rank) {
 #pragma unroll 4
     for (int k = 0; k < m; ++k) {
         const unsigned long long x = key[k];
@@ -622,12 +627,14 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
     __shared__ unsigned long long bkey[kSortCap];   // keys grouped by bucket
     __shared__ int boff[kZBuckets + 1];             // bucket counts, then offsets
     __shared__ int wsum[2][4];
+    __shared__ int deep;                            // a bucket of more than cnt / 8 charges
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int stride = ncol + 1;
 
     // segment counts h_b = P[b][c + 1] - P[b][c] over a contiguous run of b
     // per thread; their exclusive scan (segment offsets) and the sum of P[b][c]
     for (int k = t; k <= kZBuckets; k += 256) boff[k] = 0;
+    if (t == 0) deep = 0;
     const int run = (nb + 255) / 256;
     const int blo = min(t * run, nb), bhi = min(blo + run, nb);
     int h[kLocalRun], pc[kLocalRun];
@@ -709,6 +716,7 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
         boff[2 * t] = o;
         boff[2 * t + 1] = o + b0;
         if (t == 255) boff[kZBuckets] = cnt;
+        if (8 * max(b0, b1) > cnt) deep = 1;
         __syncthreads();
 #pragma unroll
         for (int v2 = 0; v2 < kPer; ++v2)
@@ -717,16 +725,36 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
         // zrow[z]: first charge whose grid z index is >= z
         for (int z = t; z <= gz; z += 256) zrow[z] = lo + boff[z * m];
         __syncthreads();
+        int rank[kPer] = {};
+        if (deep) {
+            // few values of z: against the whole column
+            unsigned long long mine[kPer];
+#pragma unroll
+            for (int v2 = 0; v2 < kPer; ++v2)
+                mine[v2] = t + 256 * v2 < cnt ? ((unsigned long long)c[v2].z << 32) | (unsigned)i[v2] : 0;
+            if (cnt <= 256)
+                rank_among<1>(bkey, cnt, mine, rank);
+            else if (cnt <= 512)
+                rank_among<2>(bkey, cnt, mine, rank);
+            else
+                rank_among<kPer>(bkey, cnt, mine, rank);
+        } else {
+#pragma unroll
+            for (int v2 = 0; v2 < kPer; ++v2) {
+                if (t + 256 * v2 < cnt) {
+                    const unsigned long long mine = ((unsigned long long)c[v2].z << 32) | (unsigned)i[v2];
+                    rank[v2] = boff[bk[v2]];
+                    const int e = boff[bk[v2] + 1];
+                    for (int k = rank[v2], e0 = e; k < e0; ++k) rank[v2] += bkey[k] < mine;
+                }
+            }
+        }
 #pragma unroll
         for (int v2 = 0; v2 < kPer; ++v2) {
             if (t + 256 * v2 < cnt) {
-                const unsigned long long mine = ((unsigned long long)c[v2].z << 32) | (unsigned)i[v2];
-                int rank = boff[bk[v2]];
-                const int e = boff[bk[v2] + 1];
-                for (int k = rank, e0 = e; k < e0; ++k) rank += bkey[k] < mine;
-                perm[lo + rank] = i[v2];
-                sorted[lo + rank] = c[v2];
-                skz[rank] = c[v2].z;
+                perm[lo + rank[v2]] = i[v2];
+                sorted[lo + rank[v2]] = c[v2];
+                skz[rank[v2]] = c[v2].z;
             }
         }
     } else {

@@ -219,6 +219,45 @@ def test_long_column_uses_all_threads(n):
     assert long <= 100.0 * short
 
 
+def layers(n, nz, seed):
+    """n charges +-1 in a 3 x 3 A footprint of a 20 x 20 x 64 A cell (one
+    column), at nz values of z."""
+    rng = np.random.default_rng(seed)
+    xyz = np.empty((n, 3), np.float32)
+    xyz[:, :2] = rng.uniform(0.5, 3.5, (n, 2))
+    xyz[:, 2] = 30.0 + 1.5 * rng.permutation(np.arange(n) % nz)
+    return xyz, rng.choice([-1.0, 1.0], n).astype(np.float32), (20.0, 20.0, 64.0)
+
+
+@pytest.mark.parametrize("nz", [1, 7, 9])
+@pytest.mark.parametrize("n", [5, 256, 257, 512, 513, 1024])
+def test_layers_in_one_column(n, nz):
+    """A column whose charges share 1 to 9 values of z: 1 and 7 leave more than
+    an eighth of it in one sort bucket (ranked against the whole column, 1, 2
+    or 4 charges per thread), 9 do not.  The order is by (z, input index)
+    either way, so the forces are those of the same charges given in that
+    order, bit for bit."""
+    xyz, q, box = layers(n, nz, 10 * n + nz)
+    order = np.argsort(xyz[:, 2], kind="stable")
+    _, f0, _ = gpu_eval(xyz, q, box, 9.0, (20, 20, 64))
+    _, f1, _ = gpu_eval(xyz[order], q[order], box, 9.0, (20, 20, 64))
+    assert np.array_equal(f0[order], f1)
+
+
+@pytest.mark.parametrize("n,factor", [(256, 2.0), (1024, 6.0)])
+def test_one_layer_sorts_in_time(n, factor):
+    """A column whose charges all share one z: 256 keys per thread take at
+    most twice the time of distinct z, and 1,024 for four charges per thread
+    at most 6 times.  (Ranked one key at a time within the bucket they took
+    2.3 and 17 times.)"""
+    box, grid = (20.0, 20.0, 64.0), (20, 20, 64)
+    xyz, q, _ = layers(n, 1, 1)
+    tied = kernel_us(xyz, q, box, 9.0, grid, "colbuild", reps=50)
+    apart = kernel_us(*wire(n, 2), 9.0, grid, "colbuild", reps=50)
+    log("case layer%d: colbuild %.1f us, distinct z %.1f us" % (n, tied, apart))
+    assert tied <= factor * apart
+
+
 @pytest.mark.parametrize("gz", [20, 128])
 def test_columns_of_tied_z(gz):
     """A 10 x 10 x 10 lattice of alternating unit charges, jittered in x and y
