@@ -401,17 +401,19 @@ __device__ __forceinline__ void pair_body(const PairArgs& a, int I, const uint4*
     // to A
     const bool cubic = CM == 1 || (CM == 0 && a.scale[0] == a.scale[1] && a.scale[0] == a.scale[2]);
     const bool units = ALPHA == 1, fixed = cubic || units;
+    const bool skew = units && !cubic;
     const float ux = a.scale[0], isx = a.inv_scale;
-    const float ry = a.scale[1] * isx, rz = a.scale[2] * isx;   // units along y, z per u
-    const float sx = units ? 1.0f : ux, sy = units ? ry * ry : a.scale[1],
-                sz = units ? rz * rz : a.scale[2];
-    const float rc2w = fixed ? a.rc2 * isx * isx : a.rc2;
-    const float irc2w = fixed ? a.inv_rc2 * ux * ux : a.inv_rc2;
+    // (in vector registers: as scalar operands of the steps they cost 1% of a
+    // whole evaluation of 90,180 charges, plain)
+    const float sx = units ? 1.0f : ux, sy = skew ? to_vgpr(a.ratio2[0]) : a.scale[1],
+                sz = skew ? to_vgpr(a.ratio2[1]) : a.scale[2];
+    const float rc2w = skew ? to_vgpr(a.rc2u) : fixed ? a.rc2 * isx * isx : a.rc2;
+    const float irc2w = skew ? to_vgpr(a.irc2u) : fixed ? a.inv_rc2 * ux * ux : a.inv_rc2;
     // q_i and the scale of the sums over j: force sum_j q_j (1/r^3 + G) d in
     // 1/u^2 (units; y and z components in their own units per u), A / u (cubic
     // powers) or A; energy in 1/u or 1/A
-    const float ffac = units ? qi * (isx * isx) : (cubic ? qi * ux : qi);
-    const float ffy = units && !cubic ? ffac * ry : ffac, ffz = units && !cubic ? ffac * rz : ffac;
+    const float ffac = skew ? qi * a.fu[0] : units ? qi * (isx * isx) : (cubic ? qi * ux : qi);
+    const float ffy = skew ? qi * a.fu[1] : ffac, ffz = skew ? qi * a.fu[2] : ffac;
     const double efac = units ? (double)qi * a.inv_scale_d : (double)qi;
     const Poly<DEG, NE> P(a, units);
     PowScale ps = {};

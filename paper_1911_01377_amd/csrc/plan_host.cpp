@@ -146,7 +146,11 @@ int build_host_plan(HostPlan* hp, const double box[3], double r_c, double b, dou
     pa.deg = deg;
     pa.alpha = alpha;
     pa.ne = ne;
-    const double u = (double)(float)(box[0] / 4294967296.0), u3 = u * u * u;
+    // a cubic cell is one whose edges' units agree in FP32, as the kernel tests
+    float unit[3];
+    for (int a = 0; a < 3; ++a) unit[a] = (float)(box[a] / 4294967296.0);
+    const bool cubic = unit[0] == unit[1] && unit[0] == unit[2];
+    const double u = cubic ? (double)unit[0] : box[0] / 4294967296.0, u3 = u * u * u;
     for (int k = 0; k <= deg; ++k) {
         pa.c[k] = (float)coef[k];
         pa.d[k] = (float)gcoef[k];
@@ -182,12 +186,16 @@ int build_host_plan(HostPlan* hp, const double box[3], double r_c, double b, dou
     p.ncol_max = p.ncmax[0] * p.ncmax[1];
     for (int a = 0; a < 3; ++a) {
         p.bin.inv_box[a] = 1.0 / box[a];
-        pa.scale[a] = (float)(box[a] / 4294967296.0);
+        pa.scale[a] = unit[a];
+        pa.fu[a] = (float)(box[a] / box[0] / (u * u));
+        if (a > 0) pa.ratio2[a - 1] = (float)((box[a] / box[0]) * (box[a] / box[0]));
         pa.scale_lo[a] = (float)(box[a] / 4294967296.0 - (double)pa.scale[a]);
     }
     pa.zinv = (float)(4294967296.0 / box[2]);
     pa.inv_scale = 1.0f / pa.scale[0];
-    pa.inv_scale_d = 1.0 / (double)pa.scale[0];
+    pa.inv_scale_d = 1.0 / u;
+    pa.rc2u = (float)(r_c / u * (r_c / u));
+    pa.irc2u = (float)(u / r_c * (u / r_c));
     {
         const double ux = (double)pa.scale[0] + (double)pa.scale_lo[0];
         const double is2 = 1.0 / (ux * ux);

@@ -77,7 +77,7 @@ struct PairArgs {
     float scale[3];       // L / 2^32: fixed-point units to A
     float scale_lo[3];    // L / 2^32 - scale: the FP32 rounding of the scale
     float inv_scale;      // 1 / scale[0] (FP32)
-    double inv_scale_d;   // 1 / scale[0] (FP64)
+    double inv_scale_d;   // 1 / u (FP64), the u of cu and du below
     float is2h, is2l;     // (1 / (scale[0] + scale_lo[0]))^2 as FP32 hi + lo
     float edge[3];        // scale / longest edge: fixed-point units to longest edges
     float rcm2;           // ((r_c + 1e-3) / longest edge)^2: the bounding-box test's reach
@@ -94,10 +94,18 @@ struct PairArgs {
     float ex[kMaxExact];        // -log2(e) rc^2 / (2 s_j^2)
     float ea[kMaxExact];        // a_j
     float eg[kMaxExact];        // -a_j / s_j^2
-    // the same for distances in fixed-point units u = scale[0] (cubic cells,
-    // the 1/r kernel): F u and (F'/r) u^3
+    // the 1/r kernel's, for distances in fixed-point units u along x (cubic
+    // cells: u = scale[0], rounded to FP32 once; others: u = L_x / 2^32):
+    // F u and (F'/r) u^3
     float cu[kMaxPolyDeg + 1], du[kMaxPolyDeg + 1];
     float eau[kMaxExact], egu[kMaxExact];
+    // and in other than cubic cells, each formed in FP64 and rounded once (every
+    // pair of the cell shares their errors; formed from the rounded scales they
+    // were 4 to 5 times as large, 1e-7 of the near energy): (L_y / L_x)^2 and
+    // (L_z / L_x)^2, r_c^2 / u^2 and its inverse, and per axis its unit over u^3
+    float ratio2[2];
+    float rc2u, irc2u;
+    float fu[3];
 };
 
 // ceil(2^32 / d): the multiplier of magic_div (device_common.h); 0 for d = 1,

@@ -113,6 +113,27 @@ def test_orthorhombic_box_and_grid():
     compare("ortho700/plain", xyz, q.astype(np.float32), box, 8.0, (20, 24, 30), 1e-6, 1e-5)
 
 
+@pytest.mark.parametrize("box", [(22.37, 22.8, 22.63), (22.53, 23.03, 21.39),
+                                 (22.87, 21.65, 22.87), (23.83, 22.61, 23.31)])
+def test_near_energy_with_the_axes_in_any_order(box):
+    """300 waters in cells whose near energy, with the axes' units relative to
+    x formed from units already rounded to FP32, differs by 1.3e-7 to 1.5e-7
+    between the three orders of the axes.  With each such factor rounded once
+    they agree to 1.5e-8 (both from the factors put into an FP64 pair sum);
+    the FP32 polynomial coefficients, whose unit is the x axis's, and the sum's
+    own rounding add to either."""
+    L = (300 / synth.WATER_DENSITY) ** (1 / 3)
+    xyz, q, _ = synth.water_box(n_mol=300, L=L, seed=77)
+    e = []
+    for ax in ([0, 1, 2], [1, 2, 0], [2, 0, 1]):
+        cell = tuple(box[a] for a in ax)
+        parts, _, _ = gpu_eval(np.ascontiguousarray(xyz[:, ax]), q, cell, 9.0, (28, 28, 28))
+        e.append(parts[0])
+    spread = (max(e) - min(e)) / abs(e[0])
+    log("case axes %s: near energies %s, spread %.2e" % (box, e, spread))
+    assert spread <= 5e-8
+
+
 def test_tall_box_long_columns():
     # a 16 x 16 x 96 A water cell (six z-replicas of a 16 A water box): 9
     # columns of ~270 charges, so the column sort takes its bitonic path
