@@ -470,6 +470,7 @@ __device__ __forceinline__ void pair_body(const PairArgs& a, int I, const uint4*
             const int nl = ru <= 0 ? 0 : min(64, (ru + kPerLane - 1) / kPerLane);
             const uint64_t live = nl >= 64 ? ~0ull : ((1ull << nl) - 1ull);
             const uint64_t m = __builtin_amdgcn_ballot_w64(near_box(pre[u])) & live;
+            if (skew) pre[u].w = __float_as_uint(__uint_as_float(pre[u].w) * kSkewCharge);
             if (__builtin_amdgcn_inverse_ballot_w64(m)) stage[w][kept + lanes_below(m)] = pre[u];
             kept += __popcll(m);
         }

@@ -187,13 +187,13 @@ int build_host_plan(HostPlan* hp, const double box[3], double r_c, double b, dou
     for (int a = 0; a < 3; ++a) {
         p.bin.inv_box[a] = 1.0 / box[a];
         pa.scale[a] = unit[a];
-        pa.fu[a] = (float)(box[a] / box[0] / (u * u));
+        pa.fu[a] = (float)(box[a] / box[0] / (u * u) / kSkewCharge);
         if (a > 0) pa.ratio2[a - 1] = (float)((box[a] / box[0]) * (box[a] / box[0]));
         pa.scale_lo[a] = (float)(box[a] / 4294967296.0 - (double)pa.scale[a]);
     }
     pa.zinv = (float)(4294967296.0 / box[2]);
     pa.inv_scale = 1.0f / pa.scale[0];
-    pa.inv_scale_d = 1.0 / u;
+    pa.inv_scale_d = cubic ? 1.0 / u : 1.0 / u / kSkewCharge;
     pa.rc2u = (float)(r_c / u * (r_c / u));
     pa.irc2u = (float)(u / r_c * (u / r_c));
     {

@@ -70,6 +70,11 @@ struct BinArgs {
     double inv_box[3];    // 1/L
 };
 
+// What the j-charges of other than cubic cells are multiplied by while staged
+// (1/r kernel; a power of two, so exact): q / r^3 in 1 / u^3 is q 2^-93 at half
+// the cell, and of charges below 1e-12 would leave the FP32 normal range
+constexpr float kSkewCharge = 0x1p64f;
+
 struct PairArgs {
     int n;
     int nc[2];            // x-y columns per axis
@@ -77,7 +82,8 @@ struct PairArgs {
     float scale[3];       // L / 2^32: fixed-point units to A
     float scale_lo[3];    // L / 2^32 - scale: the FP32 rounding of the scale
     float inv_scale;      // 1 / scale[0] (FP32)
-    double inv_scale_d;   // 1 / u (FP64), the u of cu and du below
+    double inv_scale_d;   // 1 / u (FP64), the u of cu and du below; over kSkewCharge
+                          // in other than cubic cells
     float is2h, is2l;     // (1 / (scale[0] + scale_lo[0]))^2 as FP32 hi + lo
     float edge[3];        // scale / longest edge: fixed-point units to longest edges
     float rcm2;           // ((r_c + 1e-3) / longest edge)^2: the bounding-box test's reach
@@ -102,7 +108,8 @@ struct PairArgs {
     // and in other than cubic cells, each formed in FP64 and rounded once (every
     // pair of the cell shares their errors; formed from the rounded scales they
     // were 4 to 5 times as large, 1e-7 of the near energy): (L_y / L_x)^2 and
-    // (L_z / L_x)^2, r_c^2 / u^2 and its inverse, and per axis its unit over u^3
+    // (L_z / L_x)^2, r_c^2 / u^2 and its inverse, and per axis its unit over
+    // u^3 kSkewCharge
     float ratio2[2];
     float rc2u, irc2u;
     float fu[3];

@@ -134,6 +134,23 @@ def test_near_energy_with_the_axes_in_any_order(box):
     assert spread <= 5e-8
 
 
+@pytest.mark.parametrize("form", ["plain", "bf16x3"])
+def test_small_charges_in_a_non_cubic_cell(form):
+    """Charges 2^-50 times as large give forces 2^-100 and energies 2^-100 times
+    as large: scaling by a power of two rounds nothing while every term of the
+    sums stays a normal FP32 number (1e-6: those of the spread that do not)."""
+    rng = np.random.default_rng(4)
+    box, n = (20.0, 23.5, 27.0), 700
+    xyz = (rng.uniform(0, 1, (n, 3)) * box).astype(np.float32)
+    q = rng.choice([-1.0, 1.0], n).astype(np.float32)
+    kw = dict(precision=USERIES_BF16X3) if form == "bf16x3" else {}
+    p0, f0, _ = gpu_eval(xyz, q, box, 8.0, (20, 24, 30), **kw)
+    p1, f1, _ = gpu_eval(xyz, q * np.float32(2.0 ** -50), box, 8.0, (20, 24, 30), **kw)
+    df, de = rel_rms(f1 * 2.0 ** 100, f0), abs(p1[4] * 2.0 ** 100 / p0[4] - 1.0)
+    log("case small charges/%s: dF=%.2e dE=%.2e" % (form, df, de))
+    assert df <= 1e-6 and de <= 1e-6
+
+
 def test_tall_box_long_columns():
     # a 16 x 16 x 96 A water cell (six z-replicas of a 16 A water box): 9
     # columns of ~270 charges, so the column sort takes its bitonic path
