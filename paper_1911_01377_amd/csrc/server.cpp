@@ -463,7 +463,7 @@ struct useries_server_s {
             // step serves every batch, so its grids stay fixed
             int gs[BK_COUNT];
             for (int k = 0; k < BK_COUNT; ++k)
-                gs[k] = k == BK_GATHER ? grid[k] : std::max(1, T.off[k][nb]);
+                gs[k] = k == BK_GATHER ? grid[k] : batch_grid(T.off[k][nb]);
             if ((e = enqueue_kernels(lds, lds_z, lds_g, P, exact, bins, gs))) return e;
         }
         if ((e = hipEventRecord(ring_ev[r], st))) return e;
@@ -639,6 +639,10 @@ struct useries_server_s {
         if (st) hipStreamDestroy(st);
     }
 };
+
+namespace useries {
+int batch_grid(int items) { return std::max(1, std::min(items, 1 << 21)); }
+}  // namespace useries
 
 extern "C" {
 

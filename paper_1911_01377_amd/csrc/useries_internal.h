@@ -283,6 +283,11 @@ struct BatchTable {
     int off[BK_COUNT][kMaxBatch + 1];  // work-item prefix per kernel
 };
 
+// Blocks of a batched launch (of up to 1,024 threads) that gives every work item
+// a block: at most 2^21, as HIP refuses launches of 2^32 threads (128 a cluster:
+// beyond 2.7e8 charges); the kernels stride over the rest.
+int batch_grid(int items);
+
 // Batched launchers: `grid` blocks, grid-stride over the table's items.
 hipError_t launch_encode_batch(const BatchTable* tab, const BoxDesc* desc, int grid, hipStream_t st);
 hipError_t launch_scan_batch(const BatchTable* tab, const BoxDesc* desc, int grid, hipStream_t st);

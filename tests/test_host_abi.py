@@ -131,3 +131,13 @@ def test_server_arguments_are_rejected_before_any_device_call():
     with pytest.raises(N.UseriesError) as e:
         N.useries_submit(None, N.useries_request())
     assert e.value.code == N.USERIES_EINVAL
+
+
+def test_batched_launches_stay_below_the_launch_limit():
+    """The blocks of a served step's kernels: one per work item, but never the
+    2^32 threads that HIP refuses (up to 1,024 per block, and 6.8e7 clusters at
+    the 5.4e8 charges that a request may have)."""
+    grid = getattr(N.lib(), "_ZN7useries10batch_gridEi")
+    assert [grid(k) for k in (0, 1, 7, 100000)] == [1, 1, 7, 100000]
+    for items in (1 << 21, (1 << 21) + 1, 1 << 26, (1 << 31) - 1):
+        assert 0 < grid(items) <= items and grid(items) * 1024 < 1 << 32
