@@ -415,6 +415,8 @@ __host__ __device__ constexpr int gather_slots(int P) {
 
 // Dynamic LDS of a gather block for stencil half width P (byte offsets): the
 // halo of edge brick + 2P - 1 and the per-owner weights are sized by P.
+// gather_fix's layout for P = 3 and 5, which has no range tables and fewer
+// owner slots, gather_any's for the others.
 struct GatherLds {
     int own, ownf, ownp, sphi, sw, rowtab, pbeg, poff, wtot, total;
 };
@@ -443,7 +445,7 @@ __host__ __device__ constexpr GatherLds gather_lds(int P, int waves) {
     return L;
 }
 
-// any stencil half width
+// any stencil half width but those of gather_fix
 __device__ __forceinline__ void gather_any(const GridArgs& a, int bid,
                                             const uint4* __restrict__ sorted,
                                             const int* __restrict__ perm,
@@ -860,7 +862,7 @@ __device__ __forceinline__ void gather_fix(const GridArgs& a, int bid,
     }
 }
 
-// PT = 3 or 5, or 0: a.P, any (NW = kGatherWaves)
+// PT = 3 or 5, or 0: a.P, any other (NW = kGatherWaves)
 template <int PT, int NW>
 __device__ __forceinline__ void gather_body(const GridArgs& a, int bid,
                                             const uint4* __restrict__ sorted,
@@ -901,7 +903,7 @@ __global__ void __launch_bounds__(64 * NW) k_gather(int nb,
     if (item < nb) gather_body<PT, NW>(a, item, sorted, perm, zbin, phi, fnear, forces, dyn);
 }
 
-// PT > 0 only when every box of the batch has stencil half width PT
+// every box of the batch has stencil half width PT
 template <int PT>
 __global__ void __launch_bounds__(kGatherThreads) k_gather_batch(const BatchTable* __restrict__ tab,
                                                       const BoxDesc* __restrict__ desc) {
@@ -971,7 +973,7 @@ hipError_t launch_gather_batch(const BatchTable* tab, const BoxDesc* desc, int P
     else if (P == 5)
         hipLaunchKernelGGL(k_gather_batch<5>, g, b, lds, st, tab, desc);
     else
-        hipLaunchKernelGGL(k_gather_batch<0>, g, b, lds, st, tab, desc);
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

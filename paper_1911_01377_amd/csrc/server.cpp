@@ -147,7 +147,6 @@ struct Req {
     int items[BK_COUNT] = {0};
     bool local = false;                      // two-launch binning
     size_t lds = 0, lds_z = 0, lds_g = 0;   // dynamic LDS of conv_xy, conv_z and gather
-    int P = 0;                               // stencil half width
     // shared with API threads (under the server mutex)
     int state = USERIES_PENDING;
     int err_code = USERIES_OK;
@@ -198,8 +197,8 @@ struct useries_server_s {
                                       // wait for the device)
     int grid[BK_COUNT] = {0};
     int lds_limit = 0;
-    // by the dynamic LDS sizes and the stencil half width
-    std::map<std::tuple<size_t, size_t, size_t, int, int, int>, hipGraphExec_t> graphs;
+    // by the dynamic LDS sizes, the exact Gaussians and the binning sequences
+    std::map<std::tuple<size_t, size_t, size_t, int, int>, hipGraphExec_t> graphs;
     std::vector<hipGraph_t> graph_objs;
     std::chrono::steady_clock::time_point t0 = std::chrono::steady_clock::now();
 
@@ -247,12 +246,11 @@ struct useries_server_s {
     }
 
     // the kernels of one step, in order, on the server stream
-    // P: the stencil half width shared by the step's boxes, 0 if they differ;
     // exact: the most leading far terms a box evaluates as Gaussians in its near part;
     // bins: bit 0 some box bins in two launches, bit 1 some box in four;
     // grid: blocks per kernel
-    hipError_t enqueue_kernels(size_t lds, size_t lds_z, size_t lds_g, int P, int exact,
-                               int bins, const int* grid) {
+    hipError_t enqueue_kernels(size_t lds, size_t lds_z, size_t lds_g, int exact, int bins,
+                               const int* grid) {
         const bool bf = precision == USERIES_BF16X3;
         hipError_t e;
         if ((bins & 1) && (e = launch_bin_local_batch(d_table, d_desc, grid[BK_BINLOCAL], st)))
@@ -269,14 +267,15 @@ struct useries_server_s {
         if ((e = launch_spread_batch(d_table, d_desc, grid[BK_SPREAD], st))) return e;
         if ((e = launch_conv_xy_batch(d_table, d_desc, bf, lds, grid[BK_CONV_XY], st))) return e;
         if ((e = launch_conv_z_batch(d_table, d_desc, bf, lds_z, grid[BK_CONV_Z], st))) return e;
-        if ((e = launch_gather_batch(d_table, d_desc, P, lds_g, grid[BK_GATHER], st))) return e;
+        // the form sets the stencil half width of every box
+        if ((e = launch_gather_batch(d_table, d_desc, active[0]->hp.P, lds_g, grid[BK_GATHER], st)))
+            return e;
         return launch_displace_batch(d_table, d_desc, grid[BK_DISPLACE], st);
     }
 
-    hipError_t graph_for(size_t lds, size_t lds_z, size_t lds_g, int P, int exact, int bins,
+    hipError_t graph_for(size_t lds, size_t lds_z, size_t lds_g, int exact, int bins,
                          hipGraphExec_t* out) {
-        const std::tuple<size_t, size_t, size_t, int, int, int> key(lds, lds_z, lds_g, P, exact,
-                                                                     bins);
+        const std::tuple<size_t, size_t, size_t, int, int> key(lds, lds_z, lds_g, exact, bins);
         auto it = graphs.find(key);
         if (it != graphs.end()) {
             *out = it->second;
@@ -284,7 +283,7 @@ struct useries_server_s {
         }
         hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
         if (e) return e;
-        const hipError_t el = enqueue_kernels(lds, lds_z, lds_g, P, exact, bins, grid);
+        const hipError_t el = enqueue_kernels(lds, lds_z, lds_g, exact, bins, grid);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(st, &g);
         if (el) {
@@ -426,7 +425,6 @@ struct useries_server_s {
         T.nbox = nb;
         for (int k = 0; k < BK_COUNT; ++k) T.off[k][0] = 0;
         size_t lds = 0, lds_z = 0, lds_g = 0;
-        int P = -1;
         int exact = 0;
         int bins = 0;
         for (int i = 0; i < nb; ++i) {
@@ -444,15 +442,13 @@ struct useries_server_s {
             lds = std::max(lds, R->lds);
             lds_z = std::max(lds_z, R->lds_z);
             lds_g = std::max(lds_g, R->lds_g);
-            P = (P < 0 || P == R->P) ? R->P : 0;
         }
-        P = std::max(P, 0);
         std::memcpy(ring + align_up(sizeof(BatchTable)), h_desc, sizeof(BoxDesc) * max_slots);
         if ((e = hipMemcpyAsync(d_tabdesc, ring, ring_stride, hipMemcpyHostToDevice, st)))
             return e;
         if (o.use_graph) {
             hipGraphExec_t ex = nullptr;
-            if ((e = graph_for(lds, lds_z, lds_g, P, exact, bins, &ex))) return e;
+            if ((e = graph_for(lds, lds_z, lds_g, exact, bins, &ex))) return e;
             if ((e = hipGraphLaunch(ex, st))) return e;
         } else {
             // a step launched by itself takes a block per item: blocks then leave
@@ -464,7 +460,7 @@ struct useries_server_s {
             int gs[BK_COUNT];
             for (int k = 0; k < BK_COUNT; ++k)
                 gs[k] = k == BK_GATHER ? grid[k] : batch_grid(T.off[k][nb]);
-            if ((e = enqueue_kernels(lds, lds_z, lds_g, P, exact, bins, gs))) return e;
+            if ((e = enqueue_kernels(lds, lds_z, lds_g, exact, bins, gs))) return e;
         }
         if ((e = hipEventRecord(ring_ev[r], st))) return e;
         ring_used[r] = true;
@@ -745,7 +741,6 @@ int useries_submit(useries_server_t S, const useries_request* req, uint64_t* tic
     R->lds = conv_xy_lds_bytes(hp.conv);
     R->lds_z = conv_z_lds_bytes(hp.conv);
     R->lds_g = gather_lds_bytes(hp.P);
-    R->P = hp.P;
     if (S->lds_limit > 0 && std::max({R->lds, R->lds_z, R->lds_g}) > (size_t)S->lds_limit)
         return set_last_error(USERIES_EINVAL, "grid and term count need more LDS than the device has");
     R->lay = make_layout(hp, n, r.n_evals);

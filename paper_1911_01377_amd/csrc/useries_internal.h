@@ -306,9 +306,9 @@ hipError_t launch_conv_xy_batch(const BatchTable* tab, const BoxDesc* desc, int 
                                 size_t lds, int grid, hipStream_t st);
 hipError_t launch_conv_z_batch(const BatchTable* tab, const BoxDesc* desc, int bf16x3, size_t lds,
                                int grid, hipStream_t st);
-// P: the stencil half width of every box in the batch (compiled code for 3
-// and 5), or 0 when they differ; lds >= gather_lds_bytes(P) of every box in
-// it; a box's items are its bricks and then one that writes its energy total to energies[step]
+// P: the stencil half width of every box in the batch, 3 or 5 (the two forms';
+// refused otherwise); lds >= gather_lds_bytes(P); a box's items are its bricks
+// and then one that writes its energy total to energies[step]
 hipError_t launch_gather_batch(const BatchTable* tab, const BoxDesc* desc, int P, size_t lds,
                                int grid, hipStream_t st);
 // dynamic LDS of one gather block for stencil half width P

@@ -141,3 +141,16 @@ def test_batched_launches_stay_below_the_launch_limit():
     assert [grid(k) for k in (0, 1, 7, 100000)] == [1, 1, 7, 100000]
     for items in (1 << 21, (1 << 21) + 1, 1 << 26, (1 << 31) - 1):
         assert 0 < grid(items) <= items and grid(items) * 1024 < 1 << 32
+
+
+@pytest.mark.parametrize("P", [0, 1, 2, 4, 6, 8])
+def test_batched_gather_takes_the_two_forms_stencils_only(P):
+    """Half widths other than 3 and 5 (or 0, for boxes of several) are refused
+    before any launch: the general gather does not read those boxes' layout
+    of the block's memory, and a server never makes any."""
+    import ctypes
+    fn = getattr(N.lib(), "_ZN7useries19launch_gather_batchEPKNS_10BatchTableEPKNS_7BoxDescE"
+                          "imiP12ihipStream_t")
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t, ctypes.c_int,
+                   ctypes.c_void_p]
+    assert fn(None, None, P, 1024, 1, None) == 1      # hipErrorInvalidValue
