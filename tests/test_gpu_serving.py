@@ -100,6 +100,32 @@ def test_exact_gaussians_equal_plan(degree):
         plan.close()
 
 
+@pytest.mark.parametrize("prec,grid", [
+    (USERIES_BF16X3, (90, 91, 64)), (USERIES_BF16X3, (91, 90, 30)), (USERIES_BF16X3, (96, 86, 31)),
+    (USERIES_BF16X3, (91, 90, 110)), (USERIES_PLAIN_FP32, (64, 64, 64)),
+    (USERIES_PLAIN_FP32, (72, 64, 64))])
+def test_grids_with_their_own_one_box_kernels(prec, grid):
+    """Grids of 512 and more groups of 16 columns (BF16X3: a plan's conv_z takes
+    two groups per block, in 4, 2 and 1 term groups, a server's one) and of 512
+    and 576 gather bricks (plain: a plan's gather takes 16 wavefronts up to 512,
+    a server's 8): energy and forces are the same bits, as both forms of each
+    kernel add the same terms in the same order."""
+    need_gpu()
+    xyz, q, box = synth.water_box(n_mol=1094, L=32.0, seed=12)
+    srv = Server(1 << 30, max_slots=2, precision=prec)
+    res = srv.result(srv.submit(xyz, q, box, 9.0, grid, n_evals=1))
+    srv.close()
+    plan = Plan(box, 9.0, grid, precision=prec)
+    dev = torch.device("cuda:0")
+    e, f, _ = plan.eval(torch.from_numpy(xyz).to(dev), torch.from_numpy(q).to(dev))
+    torch.cuda.synchronize()
+    e, f = float(e.cpu()[0]), f.cpu().numpy()
+    assert plan.info["n_terms_spectral"] == 0
+    plan.close()
+    assert res["energies"][0] == e
+    assert np.array_equal(res["forces"], f)
+
+
 def test_step_with_both_binning_sequences():
     """A flat 256 x 256 x 19 A cell of 200,000 random charges (69 x 69
     columns: more than the two-launch binning takes, so it bins in four
