@@ -28,11 +28,6 @@ __device__ __forceinline__ void grid_coord(uint32_t u, int n, int* gi, float* f)
     *f = (float)(uint32_t)(p & 0xffffffffull) * 2.3283064365386963e-10f;   // 2^-32
 }
 
-__device__ __forceinline__ int wrapi(int v, int n) {
-    v %= n;
-    return v < 0 ? v + n : v;
-}
-
 // v mod n for -n <= v < 2n (no integer division)
 __device__ __forceinline__ int wrap1(int v, int n) {
     v = v < 0 ? v + n : v;

@@ -578,7 +578,7 @@ __device__ __forceinline__ void bin_local_body(const BinArgs& a, int b, const fl
 // memory for every comparison, a charge per thread, 1.1 and 0.39).
 //
 // Bound: latency of two dependent rounds of scattered loads.  The block's LDS
-// (15 KB) lets all columns of the largest cells be resident at once.  With 68
+// (14 KB) lets all columns of the largest cells be resident at once.  With 68
 // KB of LDS (segment tables, sort arrays), two blocks per CU, ranks counted
 // against the whole column (bitonic beyond 256) and a search per charge for
 // its segment it took 22.4 us on 90,180 charges and 38.8 on 210,000, now 7.0
@@ -627,14 +627,12 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
     __shared__ unsigned long long bkey[kSortCap];   // keys grouped by bucket
     __shared__ int boff[kZBuckets + 1];             // bucket counts, then offsets
     __shared__ int wsum[2][4];
-    __shared__ int deep;                            // a bucket of more than cnt / 8 charges
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int stride = ncol + 1;
 
     // segment counts h_b = P[b][c + 1] - P[b][c] over a contiguous run of b
     // per thread; their exclusive scan (segment offsets) and the sum of P[b][c]
     for (int k = t; k <= kZBuckets; k += 256) boff[k] = 0;
-    if (t == 0) deep = 0;
     const int run = (nb + 255) / 256;
     const int blo = min(t * run, nb), bhi = min(blo + run, nb);
     int h[kLocalRun], pc[kLocalRun];
@@ -662,13 +660,20 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
     const int lo = ((wsum[1][0] + wsum[1][1]) + wsum[1][2]) + wsum[1][3];
     const int off0 = off;
     // list position off + j of segment b holds record 256 b + P[b][c] + j
+    auto place = [&](int u) {
+        if (blo + u < bhi) {
+            const int r0 = (blo + u) * 256 + pc[u];
+            for (int j = 0; j < h[u]; ++j) lslot[off + j] = r0 + j;
+            off += h[u];
+        }
+    };
     if (cnt <= kSortCap) {
+        place(0);
+        if (run > 1) {   // more than 65,536 charges (skipped one by one, the rest cost 0.2 us)
+            place(1);
+            if (run > 2) {
 #pragma unroll
-        for (int u = 0; u < kLocalRun; ++u) {
-            if (blo + u < bhi) {
-                const int r0 = (blo + u) * 256 + pc[u];
-                for (int j = 0; j < h[u]; ++j) lslot[off + j] = r0 + j;
-                off += h[u];
+                for (int u = 2; u < kLocalRun; ++u) place(u);
             }
         }
     }
@@ -709,14 +714,19 @@ __device__ __forceinline__ void colbuild_body(int col, int nb, int ncol, int ncx
         static_assert(kZBuckets == 512, "two buckets per thread");
         const int b0 = boff[2 * t], b1 = boff[2 * t + 1];
         const int incl = wave_incl_scan(b0 + b1);
-        if (lane == 63) wsum[0][wv] = incl;
+        const int big = __builtin_amdgcn_ballot_w64(8 * max(b0, b1) > cnt) != 0;
+        if (lane == 63) {
+            wsum[0][wv] = incl;
+            wsum[1][wv] = big;
+        }
         __syncthreads();
+        // a bucket of more than an eighth of the column
+        const bool deep = (wsum[1][0] | wsum[1][1] | wsum[1][2] | wsum[1][3]) != 0;
         int o = incl - b0 - b1;
         for (int u = 0; u < wv; ++u) o += wsum[0][u];
         boff[2 * t] = o;
         boff[2 * t + 1] = o + b0;
         if (t == 255) boff[kZBuckets] = cnt;
-        if (8 * max(b0, b1) > cnt) deep = 1;
         __syncthreads();
 #pragma unroll
         for (int v2 = 0; v2 < kPer; ++v2)

@@ -403,10 +403,13 @@ __host__ __device__ constexpr bool gather_fixed(int P) { return P == 3 || P == 5
 // lanes per owner charge
 __host__ __device__ constexpr int gather_lanes(int P) { return P == 3 ? 8 : 16; }
 // Wavefronts of a block: 16 for the P = 5 stencil while the bricks are at most
-// about two per CU (4 passes of a wavefront become 2: 6,600 charges 10.0 -> 8.8
-// us, 26,268 12.2 -> 11.7), beyond that 8, with four blocks per CU (90,180
-// charges 33.2 against 30.0 us).  P = 3: 8 (16 wavefronts 7.1 against 6.6 us at
-// 26,268 charges, 36 against 25 at 210,000).
+// two per CU (4 passes of a wavefront become 2), beyond that 8, with four blocks
+// per CU.  At 1 A spacing, 16 against 8: 216 bricks 10.6 and 11.6 us, 343 12.6
+// and 13.1, 512 13.0 and 13.6, 729 17.6 and 16.0 (65^3) or 18.7 and 16.0 (72^3),
+// 1,000 20.5 and 18.5, 1,331 25.0 and 23.0, 1,728 29.9 and 27.1, 2,197 35.2 and
+// 30.8; with fewer charges per brick the line lies lower (11,082 on 64^3 10.3
+// and 9.5) and 8 gains more beyond it (26,268 on 81^3 20.5 and 16.5).  P = 3: 8
+// (16 wavefronts 7.1 against 6.6 us at 26,268 charges, 36 against 25 at 210,000).
 constexpr int kGatherWideBricks = 512;
 // owner slots of a block: the candidates of one pass
 __host__ __device__ constexpr int gather_slots(int P) {

@@ -526,7 +526,13 @@ k_pair(int nb, const int2* __restrict__ cl_info, const int* __restrict__ cl_col,
 // them (the amplitudes beyond ne are zero).  A run-time count costs the step
 // all eight, because the compiler turns its uniform branches into selects: on
 // 26,268 charges one Gaussian (the C2 series, degree 5) took 54.7 us against
-// 26.7 compiled for one, five (Table 1 row 3, degree 7) 59.9 against 38.6.
+// 26.7 compiled for one, five (Table 1 row 3, degree 7) 59.9 against 38.6.  A
+// Gaussian costs 2.5 to 3 us there, so the counts in use have their own code:
+// one as two 30.2 against 27.6 us (Table 1 row 1, degree 7), two as three 31.4
+// against 28.5 (row 1, degree 5), three as five 38.3 against 32.9 (row 2, degree
+// 7), four as eight 45.4 against 36.7 as five (row 2, degree 5), five as eight
+// 46.7 against 38.1 (row 3, degree 7); six and seven (row 3, degrees 6 and 5, no
+// form's default) run as eight, 45.5.
 inline int exact_bucket(int ne) { return ne <= 3 ? ne : (ne <= 5 ? 5 : kMaxExact); }
 static_assert(kMaxExact == 8, "buckets 0, 1, 2, 3, 5, 8");
 

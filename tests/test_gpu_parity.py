@@ -153,8 +153,8 @@ def test_small_charges_in_a_non_cubic_cell(form):
 
 def test_tall_box_long_columns():
     # a 16 x 16 x 96 A water cell (six z-replicas of a 16 A water box): 9
-    # columns of ~270 charges, so the column sort takes its bitonic path
-    # (columns of up to 256 charges are ranked by counting)
+    # columns of ~270 charges, so the column sort takes more than one charge
+    # per thread
     x1, q1, box1 = synth.water_box(n_mol=137, L=16.0, seed=29)
     L = box1[0]
     xyz = np.concatenate([x1 + np.array([0.0, 0.0, k * L], np.float32) for k in range(6)])
@@ -191,8 +191,7 @@ def test_column_at_the_lds_sort_limit(n):
 def test_dense_column_among_many_blocks():
     """262,500 random charges in a 140 A cube and 1,500 more in a 3 x 3 A wire
     along z: a column of more than 1,024 charges, ranked from global memory,
-    whose 1,032 blocks of 256 input charges do not fit the table of segment
-    bounds.  Forces on 64 sampled charges of the wire."""
+    among 1,032 blocks of 256 input charges.  Forces on 64 sampled charges of the wire."""
     x1, q1, _ = synth.random_box(262500, (140.0, 140.0, 140.0), seed=81)
     x2, q2, _ = synth.random_box(1500, (3.0, 3.0, 140.0), seed=82)
     xyz = np.concatenate([x1, x2 + np.array([0.3, 0.3, 0.0], np.float32)]).astype(np.float32)
@@ -209,18 +208,23 @@ def test_dense_column_among_many_blocks():
 
 
 def kernel_us(xyz, q, box, rc, grid, kernel, reps=5, **kw):
-    """Mean time of one kernel of an evaluation, after a first one."""
+    """Time of one kernel of an evaluation: the mean of `reps`, best of five."""
     from paper_1911_01377_amd import Plan
     plan = Plan(box, rc, grid, **kw)
     x, qq = torch.from_numpy(xyz).cuda(), torch.from_numpy(q).cuda()
-    plan.eval(x, qq)
-    plan.timing(True)
-    for _ in range(reps):
+    best = math.inf
+    for _ in range(5):
         plan.eval(x, qq)
-    torch.cuda.synchronize()
-    ms = {name: total / max(count, 1) for name, total, count in plan.timing()}
+        torch.cuda.synchronize()
+        plan.timing(True)
+        for _ in range(reps):
+            plan.eval(x, qq)
+        torch.cuda.synchronize()
+        ms = {name: total / max(count, 1) for name, total, count in plan.timing()}
+        plan.timing(False)
+        best = min(best, 1e3 * ms[kernel])
     plan.close()
-    return 1e3 * ms[kernel]
+    return best
 
 
 def wire(n, seed):
