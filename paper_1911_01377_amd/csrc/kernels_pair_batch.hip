@@ -5,7 +5,7 @@ namespace useries {
 
 // Held to 80 registers (6 wavefronts per SIMD instead of 5), without the step
 // pipelining and its four registers.  The default kernels (degree 5 and 7 without
-// exact Gaussians) fit; 48 of the 66 spill 8 or 12 bytes per lane.
+// exact Gaussians) fit; 50 of the 66 spill 8 or 12 bytes per lane.
 template <int DEG, int NE>
 __global__ void __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu(6)))
 k_pair_batch(const BatchTable* __restrict__ tab,

@@ -458,6 +458,14 @@ __device__ __forceinline__ void pair_body(const PairArgs& a, int I, const uint4*
         int kept = 0;
         // candidates from this chunk's start (uniform: the masks below in scalar registers)
         const int rem = __builtin_amdgcn_readfirstlane(total - c * kChunkCharges);
+        if (skew) {
+#pragma unroll
+            for (int u = 0; u < kPerLane; ++u)
+                pre[u].w = __float_as_uint(__uint_as_float(pre[u].w) * kSkewCharge);
+            // shape per box: keeps this a branch (as selects it cost cubic boxes
+            // too, 0.6% of a served group of 20)
+            if (CM == 0) asm volatile("");
+        }
 #pragma unroll
         for (int u = 0; u < kPerLane; ++u) {
             // candidate u of lane l (position 4 l + u in the chunk) exists for
@@ -470,7 +478,6 @@ __device__ __forceinline__ void pair_body(const PairArgs& a, int I, const uint4*
             const int nl = ru <= 0 ? 0 : min(64, (ru + kPerLane - 1) / kPerLane);
             const uint64_t live = nl >= 64 ? ~0ull : ((1ull << nl) - 1ull);
             const uint64_t m = __builtin_amdgcn_ballot_w64(near_box(pre[u])) & live;
-            if (skew) pre[u].w = __float_as_uint(__uint_as_float(pre[u].w) * kSkewCharge);
             if (__builtin_amdgcn_inverse_ballot_w64(m)) stage[w][kept + lanes_below(m)] = pre[u];
             kept += __popcll(m);
         }
