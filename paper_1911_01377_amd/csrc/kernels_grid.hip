@@ -105,7 +105,7 @@ __device__ __forceinline__ void spread_add4(float acc[4], float xw, const float 
 // one half only); the four partials of each point are summed in a fixed order
 // at the end.
 //
-// Bound: VALU issue (77% of its slots on 90,180 charges, plain: 9,450
+// Bound: VALU issue (77% of its slots on 90,180 charges, plain: 9,480
 // instructions per brick, 38% of them the accumulation, 28% the weights).  It
 // was 55.8 us there with 3 LDS reads per charge in the accumulation, branches
 // around every stencil point in the weights and 13 integer divisions per
